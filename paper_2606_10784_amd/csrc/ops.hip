@@ -5,7 +5,7 @@
 //    the ring |d| = m) zero; spectrum F(c) by the FFT kernels (eq. (8))
 //  * numerical filter: quarter spectrum masked to |kappa| <= alpha (Sec. III-B)
 //  * near field: exact Galerkin entries of eq. (4) / the Maue form of eq. (2)
-//    minus their grid approximation, FP64, one thread per nonzero; singular
+//    minus their grid approximation, FP64, 16 lanes per nonzero; singular
 //    segment pairs use the log/regular split g = -(1/2pi) J0(kR) ln R + F(R)
 //  * anterpolation (transposed stencils, gather per active grid point) and
 //    interpolation fused with the near-field product (16 lanes per row)
@@ -215,7 +215,34 @@ struct NearGeo {
   const double* gl;   // [x16 w16 x24 w24 x32 w32]
 };
 
-__device__ void moments_self(const NearGeo& G, double h, double2 M[2][2]) {
+// The near field is built by groups of kNG = 16 lanes, one entry per group.
+// The lanes evaluate the kernel at the quadrature nodes side by side and leave
+// the terms in the group's LDS; every sum is then taken by one lane, term by
+// term in node order, so an entry's value does not depend on the grouping.
+static constexpr int kNG = 16;
+struct NearGroup {
+  int l;        // lane within the group
+  double* t;    // kNearLds doubles of LDS
+};
+static constexpr int kNearTerms = 7 * 32;             // terms of one quadrature row or panel
+static constexpr int kMaxPsiBreaks = 128;
+static constexpr int kNearLds = kNearTerms + 8 + kMaxPsiBreaks;
+
+__device__ __forceinline__ void group_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// sums held by the lanes 0..7 -> every lane: v[k] = lane k's acc
+__device__ __forceinline__ void group_share(const NearGroup& g, double acc, double* v) {
+  group_sync();
+  if (g.l < 8) g.t[kNearTerms + g.l] = acc;
+  group_sync();
+  for (int k = 0; k < 8; ++k) v[k] = g.t[kNearTerms + k];
+}
+
+__device__ void moments_self(const NearGroup& g, const NearGeo& G, double h, double2 M[2][2]) {
   const double* x24 = G.gl + 32;
   const double* w24 = G.gl + 56;
   // Q_uv(delta) coefficients (ascending powers)
@@ -240,22 +267,27 @@ __device__ void moments_self(const NearGeo& G, double h, double2 M[2][2]) {
     tm *= -z / ((m + 1.0) * (m + 1.0));
     if (fabs(tm) < 1e-20) break;
   }
-  double2 F00 = make_double2(0, 0), F10 = F00, F11 = F00;
-  for (int i = 0; i < 24; ++i) {
+  // node i: q00, q10, q11, F.x, F.y
+  for (int i = g.l; i < 24; i += kNG) {
     const double d = x24[i];
     const double2 F = green_regular(h * d, G.k);
-    const double q00 = w24[i] * (2.0 - 2.0 * d);
-    const double q10 = w24[i] * (1.0 - d);
-    const double q11 = w24[i] * (2.0 / 3.0 - d + d * d * d / 3.0);
-    F00.x += q00 * F.x; F00.y += q00 * F.y;
-    F10.x += q10 * F.x; F10.y += q10 * F.y;
-    F11.x += q11 * F.x; F11.y += q11 * F.y;
+    double* t = g.t + 5 * i;
+    t[0] = w24[i] * (2.0 - 2.0 * d);
+    t[1] = w24[i] * (1.0 - d);
+    t[2] = w24[i] * (2.0 / 3.0 - d + d * d * d / 3.0);
+    t[3] = F.x;
+    t[4] = F.y;
   }
+  group_sync();
+  double acc = 0.0, v[8];
+  if (g.l < 6)   // F00.x, F00.y, F10.x, F10.y, F11.x, F11.y
+    for (int i = 0; i < 24; ++i) acc += g.t[5 * i + (g.l >> 1)] * g.t[5 * i + 3 + (g.l & 1)];
+  group_share(g, acc, v);
   const double hh = h * h;
-  M[0][0] = make_double2(hh * (-kInv2Pi * L00 + F00.x), hh * F00.y);
-  M[1][0] = make_double2(hh * (-kInv2Pi * L10 + F10.x), hh * F10.y);
+  M[0][0] = make_double2(hh * (-kInv2Pi * L00 + v[0]), hh * v[1]);
+  M[1][0] = make_double2(hh * (-kInv2Pi * L10 + v[2]), hh * v[3]);
   M[0][1] = M[1][0];
-  M[1][1] = make_double2(hh * (-kInv2Pi * L11 + F11.x), hh * F11.y);
+  M[1][1] = make_double2(hh * (-kInv2Pi * L11 + v[4]), hh * v[5]);
 }
 
 // Breakpoints (sorted, distinct) of the polar-angle panels about a shared
@@ -265,7 +297,6 @@ __device__ void moments_self(const NearGeo& G, double h, double2 M[2][2]) {
 // before psid: pi/2 - (pi/2 - psid) 2^j); and at an acute vertex (cab > 0)
 // pi/4 and pi/4 +- delta 2^j, where ln r(psi), r^2 = 1 - sin(2 psi) cab, has
 // complex poles at distance delta = sqrt((1 - cab) / (2 cab)).
-static constexpr int kMaxPsiBreaks = 128;
 __device__ int psi_breaks(double psid, double cab, double* bp) {
   const double hp = 0.5 * kPi, q = 0.25 * kPi;
   int n = 0;
@@ -302,7 +333,7 @@ __device__ int psi_breaks(double psid, double cab, double* bp) {
 }
 
 // segments a and b share a vertex; a_first: a ends where b starts
-__device__ void moments_adjacent(const NearGeo& G, int a, int b, bool a_first, double2 M[2][2]) {
+__device__ void moments_adjacent(const NearGroup& g, const NearGeo& G, int a, int b, bool a_first, double2 M[2][2]) {
   const int N = G.N;
   const int a1 = (a + 1) % N, b1 = (b + 1) % N;
   double Vx, Vy, Pax, Pay, Pbx, Pby, t0, t1, s0, s1;
@@ -326,17 +357,20 @@ __device__ void moments_adjacent(const NearGeo& G, int a, int b, bool a_first, d
   const double k = G.k;
   // polar log part: B_ij = int int J0(kR) ln R s^i s'^j ds ds', psi over
   // the graded panels of psi_breaks
-  double B[2][2] = {{0, 0}, {0, 0}};
   const double* x32 = G.gl + 80;
   const double* w32 = G.gl + 112;
   const double psid = atan2(hb, ha);
-  double bp[kMaxPsiBreaks];
-  const int nbp = psi_breaks(psid, cab, bp);
+  double* bp = g.t + kNearTerms + 8;
+  int nbp = 0;
+  if (g.l == 0) nbp = psi_breaks(psid, cab, bp);
+  nbp = __shfl(nbp, 0, kNG);
+  group_sync();
+  double accB = 0.0;   // lanes 0..3: B_00, B_10, B_01, B_11
   for (int pnl = 0; pnl + 1 < nbp; ++pnl) {
     const double lo = bp[pnl], hi = bp[pnl + 1];
     const bool upper = lo >= psid;   // radial limit h_b / sin(psi) beyond the diagonal
     const double len = hi - lo;
-    for (int q = 0; q < 32; ++q) {
+    for (int q = g.l; q < 32; q += kNG) {
       const double ps = lo + len * x32[q];
       const double wps = len * w32[q];
       double sp, cp;
@@ -360,34 +394,56 @@ __device__ void moments_adjacent(const NearGeo& G, int a, int b, bool a_first, d
         }
         Sd[d] = acc;   // tm carries (k P r / 2)^{2m}/(m!)^2, Pe the rest
       }
-      B[0][0] += wps * Sd[0];
-      B[1][0] += wps * cp * Sd[1];
-      B[0][1] += wps * sp * Sd[1];
-      B[1][1] += wps * cp * sp * Sd[2];
+      double* t = g.t + 7 * q;
+      t[0] = wps;
+      t[1] = wps * cp;
+      t[2] = wps * sp;
+      t[3] = wps * cp * sp;
+      t[4] = Sd[0];
+      t[5] = Sd[1];
+      t[6] = Sd[2];
     }
+    group_sync();
+    if (g.l < 4) {
+      const int d = 4 + (g.l == 0 ? 0 : (g.l == 3 ? 2 : 1));
+      for (int q = 0; q < 32; ++q) accB += g.t[7 * q + g.l] * g.t[7 * q + d];
+    }
+    group_sync();
   }
+  double v[8];
+  group_share(g, accB, v);
+  const double B[2][2] = {{v[0], v[2]}, {v[1], v[3]}};
   // smooth part by 16 x 16 Gauss-Legendre in (s, s')
   const double* x16 = G.gl;
   const double* w16 = G.gl + 16;
-  double2 F[2][2];
-  for (int u = 0; u < 2; ++u)
-    for (int v = 0; v < 2; ++v) F[u][v] = make_double2(0, 0);
+  double accF = 0.0;   // lanes 0..7: F_00, F_10, F_01, F_11, re and im
   for (int i = 0; i < 16; ++i) {
     const double S = x16[i] * ha;
     const double tau = t0 + t1 * S;
-    for (int j = 0; j < 16; ++j) {
+    group_sync();
+    {
+      const int j = g.l;
       const double Sp = x16[j] * hb;
       const double sig = s0 + s1 * Sp;
-      const double R = sqrt(fmax(S * S + Sp * Sp - 2.0 * S * Sp * cab, 0.0));
+      // S^2 + S'^2 - 2 S S' cos(angle), rounded in this order
+      const double R = sqrt(fmax(fma(-(2.0 * S * Sp), cab, fma(Sp, Sp, S * S)), 0.0));
       const double2 f = green_regular(R, k);
       const double w = w16[i] * w16[j] * ha * hb;
-      const double c00 = w, c10 = w * tau, c01 = w * sig, c11 = w * tau * sig;
-      F[0][0].x += c00 * f.x; F[0][0].y += c00 * f.y;
-      F[1][0].x += c10 * f.x; F[1][0].y += c10 * f.y;
-      F[0][1].x += c01 * f.x; F[0][1].y += c01 * f.y;
-      F[1][1].x += c11 * f.x; F[1][1].y += c11 * f.y;
+      double* t = g.t + 6 * j;
+      t[0] = w;
+      t[1] = w * tau;
+      t[2] = w * sig;
+      t[3] = w * tau * sig;
+      t[4] = f.x;
+      t[5] = f.y;
     }
+    group_sync();
+    if (g.l < 8)
+      for (int j = 0; j < 16; ++j) accF += g.t[6 * j + (g.l >> 1)] * g.t[6 * j + 4 + (g.l & 1)];
   }
+  group_share(g, accF, v);
+  const double2 F[2][2] = {{make_double2(v[0], v[1]), make_double2(v[4], v[5])},
+                           {make_double2(v[2], v[3]), make_double2(v[6], v[7])}};
   // tau^u sigma^v in powers of (s, s'): alpha^u_i, beta^v_j
   for (int u = 0; u < 2; ++u)
     for (int v = 0; v < 2; ++v) {
@@ -420,7 +476,7 @@ __device__ double seg_seg_dist(double p0x, double p0y, double p1x, double p1y, d
 // than half the longer piece is split by halving the longer piece (depth at
 // most 40), so next to a short segment the nearly singular kernel is still
 // resolved; distant pairs are one box.
-__device__ void moments_disjoint(const NearGeo& G, int a, int b, double2 M[2][2]) {
+__device__ void moments_disjoint(const NearGroup& g, const NearGeo& G, int a, int b, double2 M[2][2]) {
   const int N = G.N;
   const int a1 = (a + 1) % N, b1 = (b + 1) % N;
   const double ax = G.vx[a], ay = G.vy[a], adx = G.vx[a1] - ax, ady = G.vy[a1] - ay;
@@ -428,9 +484,7 @@ __device__ void moments_disjoint(const NearGeo& G, int a, int b, double2 M[2][2]
   const double ha = G.h[a], hb = G.h[b];
   const double* x16 = G.gl;
   const double* w16 = G.gl + 16;
-  double2 acc[2][2];
-  for (int u = 0; u < 2; ++u)
-    for (int v = 0; v < 2; ++v) acc[u][v] = make_double2(0, 0);
+  double acc = 0.0;   // lanes 0..7: M_00, M_01, M_10, M_11, re and im
   constexpr int kStack = 48;
   double st[kStack][4];
   int dep[kStack];
@@ -457,73 +511,95 @@ __device__ void moments_disjoint(const NearGeo& G, int a, int b, double2 M[2][2]
       continue;
     }
     const double wt = t1 - t0, ws = s1 - s0;
-    for (int i = 0; i < 16; ++i) {
+    group_sync();
+    {
+      const int i = g.l;
       const double ti = t0 + wt * x16[i];
       const double px = ax + adx * ti, py = ay + ady * ti;
       double2 r0 = make_double2(0, 0), r1 = make_double2(0, 0);
       for (int j = 0; j < 16; ++j) {
         const double sj = s0 + ws * x16[j];
         const double dx = px - (bx + bdx * sj), dy = py - (by + bdy * sj);
-        const double2 g = green(sqrt(dx * dx + dy * dy), G.k);
+        const double2 gr = green(sqrt(dx * dx + dy * dy), G.k);
         const double w = ws * w16[j];
-        r0.x += w * g.x; r0.y += w * g.y;
-        r1.x += w * sj * g.x; r1.y += w * sj * g.y;
+        r0.x += w * gr.x; r0.y += w * gr.y;
+        r1.x += w * sj * gr.x; r1.y += w * sj * gr.y;
       }
       const double wi = wt * w16[i];
-      acc[0][0].x += wi * r0.x; acc[0][0].y += wi * r0.y;
-      acc[0][1].x += wi * r1.x; acc[0][1].y += wi * r1.y;
-      acc[1][0].x += wi * ti * r0.x; acc[1][0].y += wi * ti * r0.y;
-      acc[1][1].x += wi * ti * r1.x; acc[1][1].y += wi * ti * r1.y;
+      double* t = g.t + 6 * i;
+      t[0] = wi;
+      t[1] = wi * ti;
+      t[2] = r0.x;
+      t[3] = r0.y;
+      t[4] = r1.x;
+      t[5] = r1.y;
     }
+    group_sync();
+    if (g.l < 8)
+      for (int i = 0; i < 16; ++i) acc += g.t[6 * i + (g.l >> 2)] * g.t[6 * i + 2 + (g.l & 3)];
   }
+  double v[8];
+  group_share(g, acc, v);
   const double s = ha * hb;
   for (int u = 0; u < 2; ++u)
-    for (int v = 0; v < 2; ++v) M[u][v] = make_double2(s * acc[u][v].x, s * acc[u][v].y);
+    for (int w = 0; w < 2; ++w) M[u][w] = make_double2(s * v[4 * u + 2 * w], s * v[4 * u + 2 * w + 1]);
 }
 
-__device__ void segment_moments(const NearGeo& G, int a, int b, double2 M[2][2]) {
+__device__ void segment_moments(const NearGroup& g, const NearGeo& G, int a, int b, double2 M[2][2]) {
   const int N = G.N;
-  if (a == b) moments_self(G, G.h[a], M);
-  else if ((a + 1) % N == b) moments_adjacent(G, a, b, true, M);
-  else if ((b + 1) % N == a) moments_adjacent(G, a, b, false, M);
-  else moments_disjoint(G, a, b, M);
+  if (a == b) moments_self(g, G, G.h[a], M);
+  else if ((a + 1) % N == b) moments_adjacent(g, G, a, b, true, M);
+  else if ((b + 1) % N == a) moments_adjacent(g, G, a, b, false, M);
+  else moments_disjoint(g, G, a, b, M);
 }
 
 // grid approximation (Lambda_i^T G_grid Lambda_j) of one channel pair
-__device__ double2 grid_pair(const double* Wi, const double* Wj, int dax, int day,
+__device__ double2 grid_pair(const NearGroup& g, const double* Wi, const double* Wj, int dax, int day,
                              const double2* ks, int KS) {
-  double2 acc = make_double2(0, 0);
-  for (int e = 0; e < 16; ++e) {
-    const int se = e & 3, te = e >> 2;
-    double2 inner = make_double2(0, 0);
-    for (int f = 0; f < 16; ++f) {
-      const int sf = f & 3, tf = f >> 2;
-      const int dx = abs(dax + se - sf), dy = abs(day + te - tf);
-      const double2 kv = ks[dy * KS + dx];
-      inner.x += Wj[f] * kv.x;
-      inner.y += Wj[f] * kv.y;
-    }
-    acc.x += Wi[e] * inner.x;
-    acc.y += Wi[e] * inner.y;
+  const int e = g.l, se = e & 3, te = e >> 2;
+  double2 inner = make_double2(0, 0);
+  for (int f = 0; f < 16; ++f) {
+    const int sf = f & 3, tf = f >> 2;
+    const int dx = abs(dax + se - sf), dy = abs(day + te - tf);
+    const double2 kv = ks[dy * KS + dx];
+    inner.x += Wj[f] * kv.x;
+    inner.y += Wj[f] * kv.y;
   }
-  return acc;
+  group_sync();
+  g.t[2 * e] = inner.x;
+  g.t[2 * e + 1] = inner.y;
+  group_sync();
+  double acc = 0.0, v[8];
+  if (g.l < 2)
+    for (int q = 0; q < 16; ++q) acc += Wi[q] * g.t[2 * q + g.l];
+  group_share(g, acc, v);
+  return make_double2(v[0], v[1]);
 }
 
-__global__ void k_near_build(NearGeo G, int basis, int64_t nnz, const int32_t* __restrict__ rows,
-                             const int32_t* __restrict__ cols, const int32_t* __restrict__ anx,
-                             const int32_t* __restrict__ any, const double* W0, const double* W1,
-                             const double* W2, const double* W3, const double2* __restrict__ ks,
-                             int KS, double2* CS, double2* CN) {
-  const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= nnz) return;
+// One entry per 16-lane group.  A thread per entry left the few entries of
+// vertex-sharing segments (two per row, a serial chain of 256 + 64 series
+// evaluations) as the kernel's length, with most of the chip idle: 5.4 ms for
+// the entries of 3 328 pulses (1.0 ms here), 3.2 ms for 512 (0.42), 18.8 ms for
+// 16 384 (5.6), 80 ms for 20 001 hats (28.8).  Bound by FP64 issue in the
+// Bessel functions; two waves per SIMD (the function's own registers would
+// leave one wave per SIMD: 1.6 ms; three or four spill: 1.0 to 1.2 ms).
+static constexpr int kNearBlock = 128;
+__global__ __launch_bounds__(kNearBlock, 2) void k_near_build(
+    NearGeo G, int basis, int64_t nnz, const int32_t* __restrict__ rows, const int32_t* __restrict__ cols,
+    const int32_t* __restrict__ anx, const int32_t* __restrict__ any, const double* W0, const double* W1,
+    const double* W2, const double* W3, const double2* __restrict__ ks, int KS, double2* CS, double2* CN) {
+  __shared__ double lds[kNearBlock / kNG][kNearLds];
+  const int64_t q = (int64_t)blockIdx.x * (kNearBlock / kNG) + threadIdx.x / kNG;
+  if (q >= nnz) return;   // whole groups exit together
+  const NearGroup g{(int)(threadIdx.x % kNG), lds[threadIdx.x / kNG]};
   const int i = rows[q], j = cols[q];
   const int N = G.N;
   const int dax = anx[i] - anx[j], day = any[i] - any[j];
   double2 M[2][2];
   if (basis == AIM_PULSE) {
-    segment_moments(G, i, j, M);
-    const double2 gp = grid_pair(W0 + (size_t)i * 16, W0 + (size_t)j * 16, dax, day, ks, KS);
-    CS[q] = make_double2(M[0][0].x - gp.x, M[0][0].y - gp.y);
+    segment_moments(g, G, i, j, M);
+    const double2 gp = grid_pair(g, W0 + (size_t)i * 16, W0 + (size_t)j * 16, dax, day, ks, KS);
+    if (g.l == 0) CS[q] = make_double2(M[0][0].x - gp.x, M[0][0].y - gp.y);
     return;
   }
   // hats: pieces (segment, c0, c1): rising on i-1, falling on i
@@ -534,7 +610,7 @@ __global__ void k_near_build(NearGeo G, int basis, int64_t nnz, const int32_t* _
   for (int pa = 0; pa < 2; ++pa)
     for (int pb = 0; pb < 2; ++pb) {
       const int a = sa[pa], b = sb[pb];
-      segment_moments(G, a, b, M);
+      segment_moments(g, G, a, b, M);
       // phi_i phi_j moment: sum_uv p_u q_v M_uv with p = (c0, c1)
       const double pu[2] = {c0[pa], c1[pa]}, qv[2] = {c0[pb], c1[pb]};
       double2 pp = make_double2(0, 0);
@@ -551,10 +627,11 @@ __global__ void k_near_build(NearGeo G, int basis, int64_t nnz, const int32_t* _
       Nn.y += da * db * M[0][0].y - k2 * tt * pp.y;
     }
   const size_t oi = (size_t)i * 16, oj = (size_t)j * 16;
-  const double2 gS = grid_pair(W0 + oi, W0 + oj, dax, day, ks, KS);
-  const double2 gq = grid_pair(W1 + oi, W1 + oj, dax, day, ks, KS);
-  const double2 gx = grid_pair(W2 + oi, W2 + oj, dax, day, ks, KS);
-  const double2 gy = grid_pair(W3 + oi, W3 + oj, dax, day, ks, KS);
+  const double2 gS = grid_pair(g, W0 + oi, W0 + oj, dax, day, ks, KS);
+  const double2 gq = grid_pair(g, W1 + oi, W1 + oj, dax, day, ks, KS);
+  const double2 gx = grid_pair(g, W2 + oi, W2 + oj, dax, day, ks, KS);
+  const double2 gy = grid_pair(g, W3 + oi, W3 + oj, dax, day, ks, KS);
+  if (g.l != 0) return;
   CS[q] = make_double2(S.x - gS.x, S.y - gS.y);
   CN[q] = make_double2(Nn.x - (gq.x - k2 * (gx.x + gy.x)), Nn.y - (gq.y - k2 * (gx.y + gy.y)));
 }
@@ -1301,8 +1378,8 @@ aim_status setup_device(Ctx* c) {
     if (!ok) st = AIM_E_HIP;
     NearGeo G{c->d_vx, c->d_vy, c->d_h, c->d_tx, c->d_ty, N, t.k, d_gl};
     if (st == AIM_OK && nnz > 0) {
-      const int nb = 128;
-      hipLaunchKernelGGL(k_near_build, dim3((unsigned)((nnz + nb - 1) / nb)), dim3(nb), 0, s, G, t.basis, nnz,
+      const int per = kNearBlock / kNG;
+      hipLaunchKernelGGL(k_near_build, dim3((unsigned)((nnz + per - 1) / per)), dim3(kNearBlock), 0, s, G, t.basis, nnz,
                          d_rows, c->d_nr_col, d_anx, d_any, c->d_W[0], c->d_W[1], c->d_W[2], c->d_W[3],
                          c->d_ksmall, c->ks, c->d_CS, c->d_CN);
       if (hipGetLastError() != hipSuccess) st = AIM_E_HIP;
