@@ -130,11 +130,10 @@ def kernel_bytes(kid, inf, nch=1, nrhs=1, b=16):
     p = nch * nrhs
     if kid == 0:   # anterpolation: x, transposed stencils, U
         return N * 16 * nrhs + N * 16 * (4 + 8) + (nact + 1) * 4 + p * nact * b
-    fused = n == 1024   # the column pass reads the active points, no row pass before it
     if kid == 1:   # row FFTs: U in, T out
-        return 0 if fused else p * nact * b + nact * 4 + p * nr * n * b
-    if kid == 2:   # column FFT . spectrum . inverse: U or T in, T out, quarter spectrum once
-        return p * (nact if fused else nr * n) * b + p * nr * n * b + H * H * b
+        return p * nact * b + nact * 4 + p * nr * n * b
+    if kid == 2:   # column FFT . spectrum . inverse: T in and out, quarter spectrum once
+        return 2 * p * nr * n * b + H * H * b
     if kid == 3:   # inverse row FFTs: T in, V out
         return p * nr * n * b + p * nact * b + nact * 4
     if kid == 4:   # interpolation + near field: stencils, V, near CSR, x, y

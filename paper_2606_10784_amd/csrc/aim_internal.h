@@ -90,23 +90,11 @@ inline int fft_length(int m) {
   return n;
 }
 
-// For n = 1024 the column pass transforms the residues ky = q + 2 k', q = 0, 1,
-// by 8 x 8 x 8 (fft.hip): slot (register r, lane = 8 k0 + k1) of residue q
-// holds k' = k0 + 8 k1 + 64 r.  Stored per kxq: registers 0..3 of residue 0,
-// ky = n/2 at slot 256 (padded to 264 slots), registers 0..3 of residue 1; the
-// rest follows by evenness.
-static constexpr int kWaveCols = 1024;
 __host__ __device__ inline int spec_row_len(int n) {
-  if (n == kWaveCols) return n / 2 + 8;
   const int rl = spec_last_radix(n);
   return (n / rl / 2 + 1) * rl;
 }
 __host__ __device__ inline int ky_of_slot(int n, int j) {
-  if (n == kWaveCols) {
-    if (j >= 256 && j < 264) return n / 2;   // slot 256; 257 .. 263 are padding
-    const int q = j < 256 ? 0 : 1, p = j < 256 ? j : j - 264;
-    return q + 2 * ((p >> 3 & 7) + 8 * (p & 7) + 64 * (p >> 6));
-  }
   const int rl = spec_last_radix(n);
   return j / rl + (n / rl) * (j % rl);
 }
@@ -114,19 +102,6 @@ __host__ __device__ inline int ky_of_slot(int n, int j) {
 // ---------------------------------------------------------------------------
 // host-side geometry and tables produced by aim_setup (host_setup.cpp)
 // ---------------------------------------------------------------------------
-// Sparse row transforms of the column pass (build_row_tasks): a task is rows
-// row0 .. row0 + 64/L - 1, L = 2^lg lanes per row, T points per lane (a
-// multiple of 2), even t of even column (from x0), odd t of odd column.  The
-// tasks of a wave follow each other, and so do their slots: point t of lane
-// l at 64 t + l from the task's first slot.
-struct RowTask {
-  int32_t row0, lg, T;
-};
-struct RowWave {
-  int32_t task, ntask, slot;   // first task, tasks, first slot
-};
-static constexpr int kRowWaves = 8;        // waves that share a column-pass block's rows
-
 struct HostTables {
   int N = 0, basis = 0, m = 0, n = 0, p = 0, R = 0, nch = 1;
   double k = 0, eta = 0, eps = 0, L = 0;
@@ -143,16 +118,7 @@ struct HostTables {
   std::vector<int32_t> act_ix, act_iy;        // active points, sorted row-major
   int n_act = 0, y0 = 0, nr = 0;              // active rows [y0, y0 + nr)
   std::vector<int32_t> row_ptr;               // nr + 1 offsets into the active list
-  // column pass from the active points (n = kWaveCols): the anterpolated
-  // values sit in nslot slots, grouped by task (build_row_tasks); without
-  // tasks slot = active index
-  std::vector<RowTask> tasks;
-  std::vector<RowWave> waves;                 // kRowWaves of them, or none
-  int nslot = 0;
-  int x0 = 0, nx = 0;                         // active columns [x0, x0 + nx)
-  std::vector<int32_t> slot;                  // slot of each active point
-  std::vector<uint16_t> slot_ix;              // column - x0 of each slot (padding slots: 0 or 1)
-  // transposed stencils: for slot s, entries [at_ptr[s], at_ptr[s+1])
+  // transposed stencils: for active point a, entries [at_ptr[a], at_ptr[a+1])
   std::vector<int32_t> at_ptr, at_basis;
   std::vector<double> at_w[4];
   // near zone (CSR over basis rows, sorted columns)
@@ -222,9 +188,6 @@ struct Ctx {
   float* d_Wf[4] = {nullptr, nullptr, nullptr, nullptr};
   int32_t* d_aidx = nullptr;
   int32_t *d_act_ix = nullptr, *d_row_ptr = nullptr;
-  RowTask* d_tasks = nullptr;
-  RowWave* d_waves = nullptr;
-  uint16_t* d_slot_ix = nullptr;
   int32_t *d_at_ptr = nullptr, *d_at_basis = nullptr;
   double* d_at_w[4] = {nullptr, nullptr, nullptr, nullptr};
   float* d_at_wf[4] = {nullptr, nullptr, nullptr, nullptr};
@@ -297,15 +260,6 @@ size_t cache_clear();
 size_t cache_idle_bytes();
 // y(:, r) = op x(:, r), column strides ldx / ldy (elements), FP64 vectors
 aim_status matvec(Ctx* c, int op, int nrhs, const double2* x, int64_t ldx, double2* y, int64_t ldy);
-// Anterpolated values the column pass reads instead of transformed rows
-// (nslot > 0): nslot values per pair at U, their columns and tasks.
-struct SparseIn {
-  const void* U = nullptr;
-  const uint16_t* ix = nullptr;
-  const RowTask* task = nullptr;
-  const RowWave* wave = nullptr;
-  int nslot = 0, nx = 0;
-};
 // The column pass of a split matvec: tile sets of `pairs` pairs at `tiles`
 // (pair stride n / CB tiles of ldt x CB values), spectrum Cq, twiddles tw.
 struct ColsJob {
@@ -314,7 +268,6 @@ struct ColsJob {
   void* tiles = nullptr;
   int n = 0, nr = 0, ldt = 0, pairs = 0;
   bool f32 = false;
-  SparseIn in;
 };
 static constexpr int kColBatchMax = 32;   // tile sets per grouped column-pass launch
 bool matvec_splits(Ctx* c, int op);

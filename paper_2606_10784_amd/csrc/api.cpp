@@ -99,9 +99,7 @@ size_t footprint(const aim_params* p, int restart, const HostTables* t) {
   }
   const size_t nvals = p->basis == AIM_HAT ? 2 : 1;             // S (and N for hats) per near pair
   size_t b = 0;
-  const size_t nslot = t ? t->nslot : nact * 5 / 2 + 4096;   // U: padded to at most 2.5 times the active points
-  b += nch * R * ((size_t)tile_rows((int)nr) * n + nslot + nact) * 16;   // U, T, V
-  b += nslot * (4 + 2) + nr * sizeof(RowTask) + 1024;                           // slot offsets, columns, tasks
+  b += nch * R * ((size_t)tile_rows((int)nr) * n + 2 * nact) * 16;   // U, T, V
   b += 2 * H * spec_row_len((int)n) * 16 * (p->precision == AIM_MIXED ? 1.5 : 1.0);
   b += near * (4 + 4 + 16 * nvals) + (N + 1) * 4;               // CSR (+ row of each entry)
   if (t && t->band_w >= 0) b += (size_t)(t->band_w + 1) * N * 16 * nvals;

@@ -25,8 +25,6 @@
 // inverse pass stores only the kept rows straight to HBM.
 #include <hip/hip_ext.h>
 
-#include <type_traits>
-
 #include "aim_internal.h"
 
 namespace aim {
@@ -481,11 +479,12 @@ template <int N> constexpr int last_radix() {
 }
 
 // ---------------------------------------------------------------------------
-// tiles: CB columns per tile; columns kx and N - kx share a tile (and a
-// column-pass block) so the even-symmetric quarter spectrum is fetched once.
-// Tile b, slot c holds pair q = b*(CB/2) + c/2 + 1 (c odd: the mirror N - q);
-// the last slot pair of the last tile holds the self-mirrored columns 0 and
-// N/2.
+// tiles: CB columns per tile; columns kx and N - kx share a tile (and,
+// with two or more columns per column-pass block, a block; with one, the two
+// blocks run on one XCD) so the even-symmetric quarter spectrum is fetched
+// once.  Tile b, slot c holds pair q = b*(CB/2) + c/2 + 1 (c odd: the mirror
+// N - q); the last slot pair of the last tile holds the self-mirrored
+// columns 0 and N/2.
 // ---------------------------------------------------------------------------
 // CB is the tile width (columns per tile, the row passes' piece); CW the
 // columns one column-pass block transforms: as many as fit the LDS budget
@@ -518,20 +517,6 @@ __device__ __forceinline__ void col_block_of(int b, int& tb, int& c0) {
     tb = (b / (8 * K)) * 8 + (b & 7);
     c0 = ((b >> 3) & (K - 1)) * CW;
   }
-}
-
-// For N = 1024 a column-pass block takes a quad of columns p, N - p,
-// N/2 - p, N/2 + p (two pairs, p = 1 .. N/4 - 1; the last quad has the pairs
-// N/4 and (0, N/2)), which share their row-transform sums (sparse_rows).
-// Neighbouring p complete each other's tile lines, so each XCD (blocks are
-// dealt round-robin over 8) takes a run of p.
-template <int N> __device__ __forceinline__ int quad_of_block(int bid) {
-  static_assert(N / 4 % 8 == 0, "whole runs per XCD");
-  return (bid & 7) * (N / 32) + (bid >> 3) + 1;
-}
-// pair and slot offset (tile, first slot) of columns c = 0..3 of quad p
-template <int N> __device__ __forceinline__ int quad_pair(int p, int c) {
-  return c < 2 ? p : (p == N / 4 ? N / 2 : N / 2 - p);
 }
 
 __device__ __forceinline__ void col_of(int b, int c, int N, int CB, int& kx, int& kxq) {
@@ -896,330 +881,6 @@ __device__ __forceinline__ void cols_conv_tile(cplx<T>* buf, cplx<T>* __restrict
   }
 }
 
-// ---------------------------------------------------------------------------
-// Column pass for N = 1024: two waves per column, no block barrier inside
-// the transforms.
-//
-// The frequencies ky = q + 2 k' of one residue q are a 512-point FFT of
-// z_q[j] = W_N^{q j} x[j] (rows past N/2 are the zero padding), and the
-// inverse adds the two residues.  Wave q of a column transforms residue q in
-// place as 8 x 8 x 8 with 8 values per lane: digit a of j = 64 a + 8 b + c in
-// the registers, lane = 8 b + c; two exchanges through a wave-private LDS
-// buffer bring b, then c, into the registers.  ky order after the forward
-// transform: lane = 8 k0 + k1, register k2, k' = k0 + 8 k1 + 64 k2, which is
-// the order the spectrum is stored in.
-//
-// The inputs come from the active points themselves (sparse_rows), not from
-// transformed rows: a row holds 10 to 20 active points, so its transform at
-// one column is as many products, and the row pass with its write and read
-// of the whole tile set falls away.  Measured on a 392-row star, three
-// channels of two right-hand sides and one of two: 45.9 + 17.9 us against
-// 34.3 + 16.3 us of column pass and 16.3 + 7.3 us of row pass with one launch
-// each; the whole TE Calderon product 105.8 against 112.0 us.  Bound by FP64
-// issue and by LDS writes (a KB takes 5.8 ns per CU, a read 1.8), which
-// overlap only in part at 16 waves per CU; the row sums by the L2-to-CU rate.
-// ---------------------------------------------------------------------------
-// LDS traffic of one wave stays in program order
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  __builtin_amdgcn_sched_barrier(0);
-}
-
-// keeps the compiler from carrying values derived from a across this point
-template <typename V> __device__ __forceinline__ void opaque(V& a) { asm volatile("" : "+v"(a.x), "+v"(a.y)); }
-
-template <typename T, int N> struct WaveCols {
-  static_assert(N == 1024, "two waves per column, one residue each");
-  static constexpr int F = 512, Q = 2;
-  static constexpr int CW = 4, NT = 2 * CW * 64;
-  static constexpr int EX = 576;                      // 8 x 72: padded exchange buffer of a wave
-  static constexpr int LDS = 2 * CW * EX + 64;        // exchange buffers and W_64 table; staging and E are smaller
-  static_assert(CW * F + N / 2 <= LDS, "staging and look-up table fit");
-};
-// staging slot of (row, column c) within column c's F: rows permuted within
-// runs of 16, so that lanes along rows and lanes along (row, c) both spread
-// over the banks
-__device__ __forceinline__ int st_row(int row, int c) { return row ^ (c << 2); }
-
-// v[k] *= base g^k (conjugated when INV)
-template <typename T, bool INV>
-__device__ __forceinline__ void mul_powers(cplx<T>* v, cplx<T> base, cplx<T> g) {
-  using V = cplx<T>;
-  auto mul = [](V a, V w) { return INV ? cmulc(a, w) : cmul(a, w); };
-  opaque(g);
-  V t[4];
-  t[0] = base;
-  v[0] = mul(v[0], t[0]);
-  t[1] = cmul(base, g);
-  v[1] = mul(v[1], t[1]);
-  V g2 = cmul(g, g);
-  t[2] = cmul(base, g2);
-  v[2] = mul(v[2], t[2]);
-  t[3] = cmul(t[1], g2);
-  v[3] = mul(v[3], t[3]);
-  g2 = cmul(g2, g2);
-#pragma unroll
-  for (int k = 4; k < 8; ++k) v[k] = mul(v[k], cmul(t[k - 4], g2));
-  __builtin_amdgcn_sched_barrier(0);
-}
-
-// Forward transform, spectrum multiply and inverse transform of residue q
-// (uniform over the wave) in v.  Cr: the stored spectrum row; w64[8 k + lo]:
-// W_64^{k lo} in LDS.
-template <typename T, int N>
-__device__ __forceinline__ void wave_conv(cplx<T>* v, cplx<T>* ex, int lane, int q, cplx<T> g, const cplx<T>* w64,
-                                          const cplx<T>* __restrict__ Cr, const cplx<T>* __restrict__ tw) {
-  using V = cplx<T>;
-  const int hi = lane >> 3, lo = lane & 7;
-  V* e0 = ex + lane;                   // register digit outermost
-  V* e1 = ex + hi * 72 + lo;           // + 8 d: digit b; + 9 d: digit k1
-  V* e2 = ex + hi * 72 + lo * 9;       // + d: digit c
-  const V base = tw[lane * q];
-#pragma unroll
-  for (int t = 1; t < 8; ++t) v[t] = cmul(v[t], tw[q * t * 64]);   // uniform
-  dft8<T, false>(v);
-  mul_powers<T, false>(v, base, g);
-#pragma unroll
-  for (int d = 0; d < 8; ++d) e0[d * 72] = v[d];
-  wave_sync();
-#pragma unroll
-  for (int d = 0; d < 8; ++d) v[d] = e1[8 * d];
-  wave_sync();
-  dft8<T, false>(v);
-#pragma unroll
-  for (int k = 1; k < 8; ++k) v[k] = cmul(v[k], w64[8 * k + lo]);
-#pragma unroll
-  for (int d = 0; d < 8; ++d) e1[9 * d] = v[d];
-  wave_sync();
-  // stored spectrum slots (ky_of_slot): registers 0..3 of every lane, and for
-  // residue 0 slot 256 (lane 0, register 4).  The rest is even: -ky of (lane,
-  // r) is (63 - lane, 7 - r) for residue 1; for residue 0 lane digits
-  // (8 - k0, 7 - k1) or (0, 8 - k1) and for lane 0 register 8 - r.
-  V cv[8];
-  {
-    const int mir = q ? 63 - lane : (hi ? (8 - hi) * 8 + (7 - lo) : (lo ? 8 - lo : 64));
-#pragma unroll
-    for (int r = 0; r < 8; ++r) cv[r] = (Cr + q * 264 + (r < 4 ? r : 7 - r) * 64)[r < 4 ? lane : mir];
-  }
-#pragma unroll
-  for (int d = 0; d < 8; ++d) v[d] = e2[d];
-  wave_sync();
-  dft8<T, false>(v);
-#pragma unroll
-  for (int r = 0; r < 8; ++r) v[r] = cmul(v[r], cv[r]);
-  dft8<T, true>(v);
-#pragma unroll
-  for (int k = 1; k < 8; ++k) v[k] = cmulc(v[k], w64[8 * k + lo]);
-#pragma unroll
-  for (int d = 0; d < 8; ++d) e2[d] = v[d];
-  wave_sync();
-#pragma unroll
-  for (int d = 0; d < 8; ++d) v[d] = e1[9 * d];
-  wave_sync();
-  dft8<T, true>(v);
-#pragma unroll
-  for (int d = 0; d < 8; ++d) e1[8 * d] = v[d];
-  wave_sync();
-#pragma unroll
-  for (int d = 0; d < 8; ++d) v[d] = e0[d * 72];
-  wave_sync();
-  mul_powers<T, true>(v, base, g);
-  dft8<T, true>(v);
-#pragma unroll
-  for (int t = 1; t < 8; ++t) v[t] = cmulc(v[t], tw[q * t * 64]);
-  __builtin_amdgcn_sched_barrier(0);
-}
-
-// xor-reduction step over lane distance D within groups of 2 D lanes whose
-// halves already hold their own sums
-template <int D> __device__ __forceinline__ int lane_swap(int v) {
-  if constexpr (D == 1) return __builtin_amdgcn_mov_dpp(v, 0xB1, 0xf, 0xf, true);        // quad_perm 1,0,3,2
-  else if constexpr (D == 2) return __builtin_amdgcn_mov_dpp(v, 0x4E, 0xf, 0xf, true);   // quad_perm 2,3,0,1
-  else if constexpr (D == 4) return __builtin_amdgcn_mov_dpp(v, 0x141, 0xf, 0xf, true);  // mirror in 8
-  else if constexpr (D == 8) return __builtin_amdgcn_mov_dpp(v, 0x140, 0xf, 0xf, true);  // mirror in 16
-  else return __shfl_xor(v, D);
-}
-template <int D> __device__ __forceinline__ double lane_add(double v) {
-  return v + __hiloint2double(lane_swap<D>(__double2hiint(v)), lane_swap<D>(__double2loint(v)));
-}
-template <int D> __device__ __forceinline__ float lane_add(float v) {
-  return v + __int_as_float(lane_swap<D>(__float_as_int(v)));
-}
-
-// Row transforms of the active points at the four columns of quad p: for
-// each row, sum_i u_i W_N^{kx x_i}.  With w = W_N^{p x} = (wx, wy) the columns
-// p and N - p need u w and u conj(w), and N/2 -+ p the same with the sign
-// (-1)^x, so one look-up of w and four real products per point serve all
-// four columns when points of even and odd x are summed apart (the slots
-// alternate even and odd x).  The last quad (columns N/4, 3N/4, 0, N/2) uses
-// w = (f, 1) for even and (1, -f) for odd x, f = (-1)^{x div 2}, which keeps
-// the plain sums beside those of W_4^x.  E: nx values of w; X: the staging.
-template <typename T, int N>
-__device__ __forceinline__ void sparse_rows(cplx<T>* E, cplx<T>* X, int p, const SparseIn& in, const cplx<T>* __restrict__ U,
-                                            int nr, const cplx<T>* __restrict__ tw) {
-  using V = cplx<T>;
-  using C = WaveCols<T, N>;
-  static_assert(C::NT / 64 == kRowWaves, "row tasks are dealt to this block's waves");
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const bool last = p == N / 4;
-  const RowWave rw = in.wave[wave];
-  const V* up = U + rw.slot;
-  const uint16_t* ip = in.ix + rw.slot;
-  {
-    constexpr int PER = N / 2 / C::NT;
-    V e[PER];
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-      const int i = tid + k * C::NT;
-      const T f = (i & 2) ? -1 : 1;
-      e[k] = last ? ((i & 1) ? mk<T>(1, -f) : mk<T>(f, 1)) : tw[(p * i) & (N - 1)];
-    }
-#pragma unroll
-    for (int k = 0; k < PER; ++k)
-      if (tid + k * C::NT < in.nx) E[tid + k * C::NT] = e[k];
-  }
-  __syncthreads();
-  for (int k = rw.task; k < rw.task + rw.ntask; ++k) {
-    const RowTask tk = in.task[k];
-    // a, b, c, d: sums of u.x w.x, u.y w.y, u.x w.y, u.y w.x over even x; o*: odd
-    T a = 0, b = 0, c = 0, d = 0, oa = 0, ob = 0, oc = 0, od = 0;
-    auto add = [&](auto nn) {   // nn points per lane, all loads ahead of their uses
-      constexpr int n = decltype(nn)::value;
-      V u[n];
-      int x[n];
-#pragma unroll
-      for (int j = 0; j < n; ++j) {
-        u[j] = up[(unsigned)lane + j * 64];
-        x[j] = ip[(unsigned)lane + j * 64];
-      }
-      up += 64 * n;
-      ip += 64 * n;
-#pragma unroll
-      for (int j = 0; j < n; j += 2) {
-        const V w = E[x[j]], v = E[x[j + 1]];
-        a += u[j].x * w.x; b += u[j].y * w.y; c += u[j].x * w.y; d += u[j].y * w.x;
-        oa += u[j + 1].x * v.x; ob += u[j + 1].y * v.y; oc += u[j + 1].x * v.y; od += u[j + 1].y * v.x;
-      }
-    };
-    for (int t = 8; t <= tk.T; t += 8) add(std::integral_constant<int, 8>());
-    if (tk.T & 4) add(std::integral_constant<int, 4>());
-    if (tk.T & 2) add(std::integral_constant<int, 2>());
-    auto reduce = [&](auto dd) {
-      constexpr int D = decltype(dd)::value;
-      if ((1 << tk.lg) > D) {
-        a = lane_add<D>(a); b = lane_add<D>(b); c = lane_add<D>(c); d = lane_add<D>(d);
-        oa = lane_add<D>(oa); ob = lane_add<D>(ob); oc = lane_add<D>(oc); od = lane_add<D>(od);
-      }
-    };
-    reduce(std::integral_constant<int, 1>());
-    reduce(std::integral_constant<int, 2>());
-    reduce(std::integral_constant<int, 4>());
-    reduce(std::integral_constant<int, 8>());
-    reduce(std::integral_constant<int, 16>());
-    reduce(std::integral_constant<int, 32>());
-    const int row = tk.row0 + (lane >> tk.lg);
-    if ((lane & ((1 << tk.lg) - 1)) == 0 && row < nr) {
-      V o[4];
-      if (!last) {
-        const V ew = mk<T>(a - b, c + d), ec = mk<T>(a + b, d - c);         // even x: u w, u conj(w)
-        const V ow = mk<T>(oa - ob, oc + od), oo = mk<T>(oa + ob, od - oc);   // odd x
-        o[0] = cadd(ew, ow);
-        o[1] = cadd(ec, oo);
-        o[2] = csub(ec, oo);
-        o[3] = csub(ew, ow);
-      } else {
-        o[0] = mk<T>(a - ob, d + oc);
-        o[1] = mk<T>(a + ob, d - oc);
-        o[2] = mk<T>(c + oa, b + od);
-        o[3] = mk<T>(c - oa, b - od);
-      }
-#pragma unroll
-      for (int cc = 0; cc < 4; ++cc) X[cc * C::F + st_row(row, cc)] = o[cc];
-    }
-  }
-}
-
-// The columns of quad p of a pair's tile set Tp: from transformed rows in the
-// tiles, in place, or (SP) from the anterpolated active points
-template <typename T, int N, bool SP>
-__device__ __forceinline__ void cols_wave_quad(cplx<T>* buf, cplx<T>* __restrict__ Tp, int nr, int ldt, int p,
-                                               const cplx<T>* __restrict__ Cq, const cplx<T>* __restrict__ tw,
-                                               const SparseIn& sp, const cplx<T>* __restrict__ U) {
-  using V = cplx<T>;
-  using C = WaveCols<T, N>;
-  constexpr int F = C::F, CW = C::CW, NT = C::NT;
-  constexpr int CB = ColCfg<T, N>::CB;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int c = wave >> 1, h = wave & 1;     // column of the quad, residue ky mod 2
-  V* stc = buf + c * F + st_row(lane, c);    // + a multiple of 64 rows
-  // coalesced tile access: thread -> (row, column), PER rows RS apart
-  constexpr int PER = F * CW / NT, RS = NT / CW;
-  const int cc = tid % CW, rc = tid / CW;
-  const int pp = quad_pair<N>(p, cc) - 1;
-  V* tcol = Tp + ((size_t)(pp / (CB / 2)) * ldt + rc) * CB + (pp % (CB / 2)) * 2 + (cc & 1);
-  V* bcol = buf + cc * F + st_row(rc, cc);   // RS is a multiple of 16
-  V z[8];
-  if constexpr (SP) {
-    sparse_rows<T, N>(buf + CW * F, buf, p, sp, U, nr, tw);
-    __syncthreads();
-#pragma unroll
-    for (int t = 0; t < 8; ++t) z[t] = 64 * t + lane < nr ? stc[64 * t] : mk<T>(0, 0);
-  } else {
-    V in[PER];
-#pragma unroll
-    for (int q = 0; q < PER; ++q) in[q] = q * RS + rc < nr ? tcol[q * RS * CB] : mk<T>(0, 0);
-#pragma unroll
-    for (int q = 0; q < PER; ++q) bcol[q * RS] = in[q];
-    __syncthreads();
-#pragma unroll
-    for (int t = 0; t < 8; ++t) z[t] = stc[64 * t];
-  }
-  __syncthreads();
-  const int pr = quad_pair<N>(p, c);
-  const V* Cr = Cq + (size_t)(pr == N / 2 && !(c & 1) ? 0 : pr) * (N / 2 + 8);   // columns 0, N/2: their own rows
-  V* w64 = buf + 2 * CW * C::EX;
-  const V g = tw[lane * C::Q];
-  if (tid < 64) w64[tid] = tw[(tid >> 3) * (tid & 7) * (N / 64)];
-  __syncthreads();
-  wave_conv<T, N>(z, buf + wave * C::EX, lane, h, g, w64, Cr, tw);
-  // add the two waves' partial outputs: each wave owns the rows of half its
-  // registers, gives the other half away, and leaves the sums in the staging
-  // for coalesced stores
-  __syncthreads();
-  auto give = [&](auto hh) {
-    constexpr int O = 4 * (1 - decltype(hh)::value);
-#pragma unroll
-    for (int t = O; t < O + 4; ++t) stc[64 * t] = z[t];
-  };
-  auto add = [&](auto hh) {
-    constexpr int O = 4 * decltype(hh)::value;
-#pragma unroll
-    for (int t = O; t < O + 4; ++t) stc[64 * t] = cadd(stc[64 * t], z[t]);
-  };
-  if (h == 0) give(std::integral_constant<int, 0>());
-  else give(std::integral_constant<int, 1>());
-  __syncthreads();
-  if (h == 0) add(std::integral_constant<int, 0>());
-  else add(std::integral_constant<int, 1>());
-  __syncthreads();
-#pragma unroll
-  for (int q = 0; q < PER; ++q)
-    if (q * RS + rc < nr) tcol[q * RS * CB] = bcol[q * RS];
-}
-
-template <typename T, int N, bool SP>
-__global__ __launch_bounds__((WaveCols<T, N>::NT), 4) void k_cols_wave(
-    cplx<T>* __restrict__ Tb, int nr, int ldt, const cplx<T>* __restrict__ Cq, const cplx<T>* __restrict__ tw,
-    SparseIn in) {
-  __shared__ cplx<T> buf[WaveCols<T, N>::LDS];
-  cols_wave_quad<T, N, SP>(buf, Tb + (size_t)blockIdx.y * N * ldt, nr, ldt, quad_of_block<N>(blockIdx.x), Cq, tw, in,
-                           (const cplx<T>*)in.U + (size_t)blockIdx.y * in.nslot);
-}
-
 template <typename T, int N, int MODE>
 __global__ __launch_bounds__((ColCfg<T, N>::NT)) void k_cols(
     cplx<T>* __restrict__ Tb, int nr, int ldt, const cplx<T>* __restrict__ Cq,
@@ -1261,7 +922,6 @@ struct ColBatch {
   void* tile[kMax];
   int nr[kMax];
   int ldt[kMax];
-  SparseIn in[kMax];
 };
 
 template <typename T, int N>
@@ -1275,15 +935,6 @@ __global__ __launch_bounds__((ColCfg<T, N>::NT)) void k_cols_group(ColBatch batc
   col_block_of<T, N>(blockIdx.x, tb, c0);
   V* tile = (V*)batch.tile[e] + (size_t)tb * batch.ldt[e] * CB;
   cols_conv_tile<T, N>(buf, tile, batch.nr[e], tb, c0, Cq, tw);
-}
-
-template <typename T, int N, bool SP>
-__global__ __launch_bounds__((WaveCols<T, N>::NT), 4) void k_cols_wave_group(
-    ColBatch batch, const cplx<T>* __restrict__ Cq, const cplx<T>* __restrict__ tw) {
-  __shared__ cplx<T> buf[WaveCols<T, N>::LDS];
-  const int e = blockIdx.y;
-  cols_wave_quad<T, N, SP>(buf, (cplx<T>*)batch.tile[e], batch.nr[e], batch.ldt[e],
-                           quad_of_block<N>(blockIdx.x), Cq, tw, batch.in[e], (const cplx<T>*)batch.in[e].U);
 }
 
 // ---------------------------------------------------------------------------
@@ -1329,45 +980,21 @@ aim_status launch_rows_inv(int n, const cplx<T>* Tb, int nr, int ldt, const int3
   return hipGetLastError() == hipSuccess ? AIM_OK : AIM_E_HIP;
 }
 
-// The column pass: from transformed rows in Tb, or from the active points of
-// `in` (in.nslot > 0, n = kWaveCols).  mode 1: the set-up FFT.
-template <typename T, int N>
-void cols_wave(cplx<T>* Tb, int nr, int ldt, int pairs, const cplx<T>* Cq, const cplx<T>* tw, const SparseIn& in,
-               hipStream_t s, hipEvent_t ev_start, hipEvent_t ev_stop) {
-  const dim3 g(N / WaveCols<T, N>::CW, pairs), b(WaveCols<T, N>::NT);
-  if (in.nslot > 0)
-    hipExtLaunchKernelGGL((k_cols_wave<T, N, true>), g, b, 0, s, ev_start, ev_stop, 0, Tb, nr, ldt, Cq, tw, in);
-  else
-    hipExtLaunchKernelGGL((k_cols_wave<T, N, false>), g, b, 0, s, ev_start, ev_stop, 0, Tb, nr, ldt, Cq, tw, in);
-}
-template <typename T, int N>
-void cols_wave_group(const ColBatch& bt, int count, bool sparse, const cplx<T>* Cq, const cplx<T>* tw,
-                     hipStream_t s) {
-  const dim3 g(N / WaveCols<T, N>::CW, count), b(WaveCols<T, N>::NT);
-  if (sparse)
-    hipLaunchKernelGGL((k_cols_wave_group<T, N, true>), g, b, 0, s, bt, Cq, tw);
-  else
-    hipLaunchKernelGGL((k_cols_wave_group<T, N, false>), g, b, 0, s, bt, Cq, tw);
-}
-
 template <typename T>
 aim_status launch_cols(int n, int mode, cplx<T>* Tb, int nr, int ldt, int pairs, const cplx<T>* Cq,
-                       const cplx<T>* tw, const SparseIn& in, hipStream_t s, hipEvent_t ev_start, hipEvent_t ev_stop) {
+                       const cplx<T>* tw, hipStream_t s, hipEvent_t ev_start, hipEvent_t ev_stop) {
   // kept rows lie in the unpadded half
   if (mode == 0 && (nr < 1 || nr > n / 2 || ldt < nr)) return AIM_E_ARG;
-  if (in.nslot > 0 && (mode != 0 || n != kWaveCols || in.nx > n / 2)) return AIM_E_ARG;
   switch (n) {
-#define CASE(NN)                                                                                                     \
-  case NN: {                                                                                                         \
-    if (mode != 0)                                                                                                   \
-      hipLaunchKernelGGL((k_cols<T, NN, 1>), dim3(NN / ColCfg<T, NN>::CW, pairs), dim3(ColCfg<T, NN>::NT), 0, s, Tb, \
-                         nr, ldt, Cq, tw);                                                                           \
-    else if constexpr (NN == kWaveCols)                                                                           \
-      cols_wave<T, NN>(Tb, nr, ldt, pairs, Cq, tw, in, s, ev_start, ev_stop);                                        \
-    else                                                                                                             \
-      hipExtLaunchKernelGGL((k_cols<T, NN, 0>), dim3(NN / ColCfg<T, NN>::CW, pairs), dim3(ColCfg<T, NN>::NT), 0, s,  \
-                            ev_start, ev_stop, 0, Tb, nr, ldt, Cq, tw);                                              \
-    break;                                                                                                           \
+#define CASE(NN)                                                                          \
+  case NN: {                                                                              \
+    dim3 g(NN / ColCfg<T, NN>::CW, pairs);                                                \
+    if (mode == 0)                                                                        \
+      hipExtLaunchKernelGGL((k_cols<T, NN, 0>), g, dim3(ColCfg<T, NN>::NT), 0, s, ev_start, ev_stop, 0, \
+                            Tb, nr, ldt, Cq, tw);                                         \
+    else                                                                                  \
+      hipLaunchKernelGGL((k_cols<T, NN, 1>), g, dim3(ColCfg<T, NN>::NT), 0, s, Tb, nr, ldt, Cq, tw); \
+    break;                                                                                \
   }
     AIM_FOR_SIZES(CASE)
 #undef CASE
@@ -1387,31 +1014,24 @@ int col_block(int n, bool f32) {
   return 0;
 }
 
-// grouped column pass over `count` tile sets (count <= ColBatch::kMax), all
-// of them from transformed rows or all from active points
+// grouped column pass over `count` tile sets (count <= ColBatch::kMax)
 template <typename T>
-aim_status launch_cols_group(int n, int count, void* const* tiles, const int* nr, const int* ldt, const SparseIn* in,
+aim_status launch_cols_group(int n, int count, void* const* tiles, const int* nr, const int* ldt,
                              const cplx<T>* Cq, const cplx<T>* tw, hipStream_t s) {
   if (count < 1 || count > ColBatch::kMax) return AIM_E_ARG;
   ColBatch bt;
-  const bool sparse = in[0].nslot > 0;
   for (int e = 0; e < ColBatch::kMax; ++e) {
     const int q = e < count ? e : 0;
-    if (nr[q] < 1 || nr[q] > n / 2 || ldt[q] < nr[q] || (in[q].nslot > 0) != sparse || in[q].nx > n / 2) return AIM_E_ARG;
+    if (nr[q] < 1 || nr[q] > n / 2 || ldt[q] < nr[q]) return AIM_E_ARG;
     bt.tile[e] = tiles[q];
     bt.nr[e] = nr[q];
     bt.ldt[e] = ldt[q];
-    bt.in[e] = in[q];
   }
-  if (sparse && n != kWaveCols) return AIM_E_ARG;
   switch (n) {
 #define CASE(NN)                                                                                              \
   case NN:                                                                                                    \
-    if constexpr (NN == kWaveCols)                                                                         \
-      cols_wave_group<T, NN>(bt, count, sparse, Cq, tw, s);                                                   \
-    else                                                                                                      \
-      hipLaunchKernelGGL((k_cols_group<T, NN>), dim3(NN / ColCfg<T, NN>::CW, count), dim3(ColCfg<T, NN>::NT), 0, \
-                         s, bt, Cq, tw);                                                                      \
+    hipLaunchKernelGGL((k_cols_group<T, NN>), dim3(NN / ColCfg<T, NN>::CW, count), dim3(ColCfg<T, NN>::NT), 0, \
+                       s, bt, Cq, tw);                                                                        \
     break;
     AIM_FOR_SIZES(CASE)
 #undef CASE
@@ -1442,12 +1062,12 @@ template aim_status launch_rows_inv<double>(int, const double2*, int, int, const
 template aim_status launch_rows_inv<float>(int, const float2*, int, int, const int32_t*, const int32_t*, int,
                                            float2*, int, const float2*, hipStream_t);
 template aim_status launch_cols<double>(int, int, double2*, int, int, int, const double2*, const double2*,
-                                        const SparseIn&, hipStream_t, hipEvent_t, hipEvent_t);
-template aim_status launch_cols<float>(int, int, float2*, int, int, int, const float2*, const float2*,
-                                       const SparseIn&, hipStream_t, hipEvent_t, hipEvent_t);
-template aim_status launch_cols_group<double>(int, int, void* const*, const int*, const int*, const SparseIn*,
-                                              const double2*, const double2*, hipStream_t);
-template aim_status launch_cols_group<float>(int, int, void* const*, const int*, const int*, const SparseIn*,
-                                             const float2*, const float2*, hipStream_t);
+                                        hipStream_t, hipEvent_t, hipEvent_t);
+template aim_status launch_cols<float>(int, int, float2*, int, int, int, const float2*, const float2*, hipStream_t,
+                                       hipEvent_t, hipEvent_t);
+template aim_status launch_cols_group<double>(int, int, void* const*, const int*, const int*, const double2*,
+                                              const double2*, hipStream_t);
+template aim_status launch_cols_group<float>(int, int, void* const*, const int*, const int*, const float2*,
+                                             const float2*, hipStream_t);
 
 }  // namespace aim

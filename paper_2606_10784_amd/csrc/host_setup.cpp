@@ -95,105 +95,6 @@ static inline void lagrange4(double t, double l[4]) {
   l[3] = (t + 1.0) * t * (t - 1.0) / 6.0;
 }
 
-// Splits the active rows into tasks of the column pass's sparse row
-// transforms and deals them to the waves of a block, longest first to the
-// least loaded.  Aligned blocks of 64 rows are halved (doubling the lanes per
-// row) while that lowers the cost, T + 4 + 3 log2 L iterations (a task's end
-// and a halving step of its lane reduction cost about that many), or T
-// exceeds 0.6 of a wave's even share, so rows of very different lengths
-// neither pad each other nor leave one wave behind.  Sets the slots; leaves
-// tasks empty (slot = active index) when the padded points exceed 28 per row
-// or 2.5 times the active ones: the sums of every column block then cost
-// more than transforming the rows once (502 rows of a 2048-point embedding,
-// by active points per row: one right-hand side 45.0 against 49.0 us at 15,
-// 46.2 against 48.7 at 38; eight 209 against 208 us at 15, 230 against 213 at
-// 31).
-static void build_row_tasks(HostTables& t) {
-  const int nr = t.nr;
-  t.slot.resize(t.n_act);
-  std::iota(t.slot.begin(), t.slot.end(), 0);
-  t.nslot = t.n_act;
-  t.tasks.clear();
-  t.waves.clear();
-  if (t.n != kWaveCols) return;
-  std::vector<int> par(nr);   // the larger of a row's even and odd point counts
-  for (int r = 0; r < nr; ++r) {
-    int odd = 0;
-    for (int a = t.row_ptr[r]; a < t.row_ptr[r + 1]; ++a) odd += (t.act_ix[a] - t.x0) & 1;
-    par[r] = std::max(odd, t.row_ptr[r + 1] - t.row_ptr[r] - odd);
-  }
-  auto points = [&](int r0, int G, int lg) {
-    int h = 0;
-    for (int r = r0; r < std::min(nr, r0 + G); ++r) h = std::max(h, (par[r] + (1 << lg) - 1) >> lg);
-    return 2 * h;
-  };
-  auto cost = [](int T, int lg) { return T + 4.0 + 3.0 * lg; };
-  int cap = 1 << 30;
-  // best split of the 64 >> lg rows from r0; appends the tasks when out is given
-  auto split = [&](auto&& self, int r0, int lg, std::vector<RowTask>* out) -> double {
-    const int G = 64 >> lg;
-    if (r0 >= nr) return 0.0;
-    const int T = points(r0, G, lg);
-    const double whole = cost(T, lg);
-    double half = 1e300;
-    if (G > 1) half = self(self, r0, lg + 1, nullptr) + self(self, r0 + G / 2, lg + 1, nullptr);
-    const bool cut = G > 1 && (half < whole || T > cap);
-    if (out) {
-      if (cut) {
-        self(self, r0, lg + 1, out);
-        self(self, r0 + G / 2, lg + 1, out);
-      } else {
-        out->push_back({r0, lg, T});
-      }
-    }
-    return cut ? half : whole;
-  };
-  std::vector<RowTask> tasks;
-  std::vector<RowWave> waves;
-  int64_t slots = 0;
-  double total = 0;
-  for (int r0 = 0; r0 < nr; r0 += 64) total += split(split, r0, 0, nullptr);
-  cap = std::max(8, (int)(0.6 * total / kRowWaves));
-  std::vector<RowTask> part;
-  for (int r0 = 0; r0 < nr; r0 += 64) split(split, r0, 0, &part);
-  std::stable_sort(part.begin(), part.end(),
-                   [&](const RowTask& a, const RowTask& b) { return cost(a.T, a.lg) > cost(b.T, b.lg); });
-  std::vector<RowTask> own[kRowWaves];
-  double load[kRowWaves] = {};
-  for (const RowTask& k : part) {
-    const int w = (int)(std::min_element(load, load + kRowWaves) - load);
-    own[w].push_back(k);
-    load[w] += cost(k.T, k.lg);
-  }
-  for (const std::vector<RowTask>& o : own) {
-    waves.push_back({(int32_t)tasks.size(), (int32_t)o.size(), (int32_t)slots});
-    for (const RowTask& k : o) {
-      tasks.push_back(k);
-      slots += 64 * (int64_t)k.T;
-    }
-  }
-  if (slots > (int64_t)28 * nr || slots > 2.5 * t.n_act + 4096) return;
-  t.nslot = (int)slots;
-  t.slot_ix.assign(t.nslot, 0);
-  int base = 0;
-  for (const RowTask& k : tasks) {
-    const int L = 1 << k.lg;
-    for (int j = 0; j < 64 * k.T; ++j) t.slot_ix[base + j] = j / 64 & 1;   // padding: any column of that parity
-    for (int r = k.row0; r < std::min(nr, k.row0 + 64 / L); ++r) {
-      int seen[2] = {0, 0};
-      for (int a = t.row_ptr[r]; a < t.row_ptr[r + 1]; ++a) {
-        const int x = t.act_ix[a] - t.x0, q = seen[x & 1]++;
-        const int s = base + 64 * (2 * (q / L) + (x & 1)) + (r - k.row0) * L + q % L;
-        t.slot[a] = s;
-        t.slot_ix[s] = (uint16_t)x;
-      }
-    }
-    base += 64 * k.T;
-  }
-  t.tasks.swap(tasks);
-  t.waves.swap(waves);
-}
-
 aim_status build_host_tables(const aim_params* p, HostTables& t, std::string& err) {
   if (!p || !p->xy) { err = "null params"; return AIM_E_ARG; }
   const int N = p->n_vertices;
@@ -411,24 +312,21 @@ aim_status build_host_tables(const aim_params* p, HostTables& t, std::string& er
   t.row_ptr.assign(t.nr + 1, 0);
   for (int a = 0; a < t.n_act; ++a) t.row_ptr[t.act_iy[a] - t.y0 + 1]++;
   for (int r = 0; r < t.nr; ++r) t.row_ptr[r + 1] += t.row_ptr[r];
-  t.x0 = *std::min_element(t.act_ix.begin(), t.act_ix.end());
-  t.nx = *std::max_element(t.act_ix.begin(), t.act_ix.end()) - t.x0 + 1;
-  build_row_tasks(t);
 
-  // transposed map rows (slot of a grid point -> contributing bases), for the
-  // gather; padding entries are left out (padding slots gather nothing)
-  t.at_ptr.assign(t.nslot + 1, 0);
+  // transposed map rows (grid point -> contributing bases), for the gather;
+  // padding entries are left out
+  t.at_ptr.assign(t.n_act + 1, 0);
   size_t nent = 0;
   for (int j = 0; j < N; ++j)
-    for (int e = 0; e < cnt[j]; ++e) t.at_ptr[t.slot[t.aidx[(size_t)j * S + e]] + 1]++, ++nent;
-  for (int a = 0; a < t.nslot; ++a) t.at_ptr[a + 1] += t.at_ptr[a];
+    for (int e = 0; e < cnt[j]; ++e) t.at_ptr[t.aidx[(size_t)j * S + e] + 1]++, ++nent;
+  for (int a = 0; a < t.n_act; ++a) t.at_ptr[a + 1] += t.at_ptr[a];
   t.at_basis.assign(nent, 0);
   for (int c = 0; c < 4; ++c) t.at_w[c].assign(c < nch ? nent : 0, 0.0);
   {
     std::vector<int32_t> fill(t.at_ptr.begin(), t.at_ptr.end() - 1);
     for (int j = 0; j < N; ++j)
       for (int e = 0; e < cnt[j]; ++e) {
-        int a = t.slot[t.aidx[(size_t)j * S + e]];
+        int a = t.aidx[(size_t)j * S + e];
         int pos = fill[a]++;
         t.at_basis[pos] = j;
         for (int c = 0; c < nch; ++c) t.at_w[c][pos] = t.W[c][(size_t)j * S + e];

@@ -29,11 +29,11 @@ aim_status launch_rows_inv(int n, const cplx<T>* Tb, int nr, int ldt, const int3
                            const cplx<T>* tw, hipStream_t s);
 template <typename T>
 aim_status launch_cols(int n, int mode, cplx<T>* Tb, int nr, int ldt, int pairs, const cplx<T>* Cq,
-                       const cplx<T>* tw, const SparseIn& in, hipStream_t s, hipEvent_t ev_start = nullptr,
+                       const cplx<T>* tw, hipStream_t s, hipEvent_t ev_start = nullptr,
                        hipEvent_t ev_stop = nullptr);
 aim_status launch_rows_fft_inplace(int n, double2* A, const double2* tw, hipStream_t s);
 template <typename T>
-aim_status launch_cols_group(int n, int count, void* const* tiles, const int* nr, const int* ldt, const SparseIn* in,
+aim_status launch_cols_group(int n, int count, void* const* tiles, const int* nr, const int* ldt,
                              const cplx<T>* Cq, const cplx<T>* tw, hipStream_t s);
 int col_block(int n, bool f32);
 
@@ -1207,7 +1207,7 @@ aim_status acquire_spectrum(Ctx* c, double keps) {
   }
   hipLaunchKernelGGL(k_sample_kernel, dim3((n + 255) / 256, n), dim3(256), 0, s, m, n, keps, cfull);
   aim_status st = launch_rows_fft_inplace(n, cfull, c->d_tw, s);
-  if (st == AIM_OK) st = launch_cols<double>(n, 1, cfull, n, n, 1, nullptr, c->d_tw, SparseIn(), s);
+  if (st == AIM_OK) st = launch_cols<double>(n, 1, cfull, n, n, 1, nullptr, c->d_tw, s);
   if (st == AIM_OK) {
     hipLaunchKernelGGL(k_extract_spectrum, dim3((spec_row_len(n) + 255) / 256, H), dim3(256), 0, s, n, cfull, e->C, e->Cf);
     if (hipStreamSynchronize(s) != hipSuccess) st = AIM_E_HIP;
@@ -1306,16 +1306,7 @@ aim_status setup_device(Ctx* c) {
     }
   }
   TRY(upload(c, &c->d_aidx, t.aidx.data(), t.aidx.size() * 4));
-  // with row tasks the columns count from x0: the circulant product commutes
-  // with cyclic shifts
-  std::vector<int32_t> ixs(t.act_ix);
-  for (int32_t& v : ixs) v -= t.tasks.empty() ? 0 : t.x0;
-  TRY(upload(c, &c->d_act_ix, ixs.data(), ixs.size() * 4));
-  if (!t.tasks.empty()) {
-    TRY(upload(c, &c->d_tasks, t.tasks.data(), t.tasks.size() * sizeof(RowTask)));
-    TRY(upload(c, &c->d_waves, t.waves.data(), t.waves.size() * sizeof(RowWave)));
-    TRY(upload(c, &c->d_slot_ix, t.slot_ix.data(), t.slot_ix.size() * sizeof(uint16_t)));
-  }
+  TRY(upload(c, &c->d_act_ix, t.act_ix.data(), t.act_ix.size() * 4));
   TRY(upload(c, &c->d_row_ptr, t.row_ptr.data(), t.row_ptr.size() * 4));
   TRY(upload(c, &c->d_at_ptr, t.at_ptr.data(), t.at_ptr.size() * 4));
   TRY(upload(c, &c->d_at_basis, t.at_basis.data(), t.at_basis.size() * 4));
@@ -1414,7 +1405,7 @@ aim_status setup_device(Ctx* c) {
   c->nch_max = (t.basis == AIM_HAT) ? 3 : 1;
   const size_t pairs = (size_t)c->nch_max * c->max_rhs;
   const size_t be = 16;   // FP64 complex (FP32 uses the first half)
-  TRY(dev_alloc(c, &c->d_U, pairs * t.nslot * be));
+  TRY(dev_alloc(c, &c->d_U, pairs * t.n_act * be));
   TRY(dev_alloc(c, &c->d_V, pairs * t.n_act * be));
   TRY(dev_alloc(c, &c->d_T, pairs * (size_t)tile_rows(t.nr) * n * be));
   TRY(dev_alloc(c, (void**)&c->d_tmp1, (size_t)N * c->max_rhs * 16));
@@ -1486,7 +1477,7 @@ aim_status apply_filter_analytic(Ctx* c, double alpha) {
     st = hipGetLastError() == hipSuccess ? AIM_OK : AIM_E_HIP;
   }
   if (st == AIM_OK) st = launch_rows_fft_inplace(n, cfull, c->d_tw, s);
-  if (st == AIM_OK) st = launch_cols<double>(n, 1, cfull, n, n, 1, nullptr, c->d_tw, SparseIn(), s);
+  if (st == AIM_OK) st = launch_cols<double>(n, 1, cfull, n, n, 1, nullptr, c->d_tw, s);
   if (st == AIM_OK) {
     hipLaunchKernelGGL(k_extract_spectrum, dim3((spec_row_len(n) + 255) / 256, H), dim3(256), 0, s, n, cfull, c->own_Ca,
                        c->own_Caf);
@@ -1504,9 +1495,9 @@ aim_status apply_filter_analytic(Ctx* c, double alpha) {
 }
 
 // grid part: V = [F^-1 (Chat . F(Lambda x))]_restr for nch channels, in
-// three steps: anterpolation and, without row tasks, forward row FFTs
-// (grid_pre), the column pass (launch_cols, or one grouped launch for several
-// contexts), inverse row FFTs (grid_post)
+// three steps: anterpolation and forward row FFTs (grid_pre), the column
+// pass (launch_cols, or one grouped launch for several contexts), inverse
+// row FFTs (grid_post)
 template <typename T>
 static const cplx<T>* grid_spectrum(Ctx* c, bool filt) {
   const bool f32 = sizeof(T) == 4;
@@ -1518,36 +1509,25 @@ static const cplx<T>* grid_twiddles(Ctx* c) {
   return sizeof(T) == 4 ? (const cplx<T>*)c->d_twf : (const cplx<T>*)c->d_tw;
 }
 
-static SparseIn sparse_in(Ctx* c) {
-  const HostTables& t = c->t;
-  SparseIn in;
-  if (t.tasks.empty()) return in;
-  in.U = c->d_U;
-  in.ix = c->d_slot_ix;
-  in.task = c->d_tasks;
-  in.wave = c->d_waves;
-  in.nslot = t.nslot;
-  in.nx = t.nx;
-  return in;
-}
-
 template <typename T>
 static aim_status grid_pre(Ctx* c, const int* chans, int nch, int nrhs, const double2* x, int64_t ldx) {
   HostTables& t = c->t;
   hipStream_t s = c->stream;
+  const int pairs = nch * nrhs;
   cplx<T>* U = (cplx<T>*)c->d_U;
+  cplx<T>* Tb = (cplx<T>*)c->d_T;
   const bool f32 = sizeof(T) == 4;
   // a single rhs keeps one sum per lane; batches share the entry loads
   const int arb = nrhs >= kAnterpRhs ? kAnterpRhs : 1;
-  dim3 ga((unsigned)(((size_t)t.nslot * 16 + 255) / 256), nch * ((nrhs + arb - 1) / arb));
+  dim3 ga((unsigned)(((size_t)t.n_act * 16 + 255) / 256), nch * ((nrhs + arb - 1) / arb));
   {
   ProfScope ps(c, AIM_K_ANTERP);
 #define AIM_ANTERP(TW, WS)                                                                                          \
   if (arb == 1)                                                                                                     \
-    hipLaunchKernelGGL((k_anterp<T, TW, 1>), ga, dim3(256), 0, s, t.nslot, nrhs, c->d_at_ptr, c->d_at_basis,       \
+    hipLaunchKernelGGL((k_anterp<T, TW, 1>), ga, dim3(256), 0, s, t.n_act, nrhs, c->d_at_ptr, c->d_at_basis,       \
                        WS[chans[0]], WS[chans[nch > 1 ? 1 : 0]], WS[chans[nch > 2 ? 2 : 0]], x, ldx, U);             \
   else                                                                                                              \
-    hipLaunchKernelGGL((k_anterp<T, TW, kAnterpRhs>), ga, dim3(256), 0, s, t.nslot, nrhs, c->d_at_ptr,             \
+    hipLaunchKernelGGL((k_anterp<T, TW, kAnterpRhs>), ga, dim3(256), 0, s, t.n_act, nrhs, c->d_at_ptr,             \
                        c->d_at_basis, WS[chans[0]], WS[chans[nch > 1 ? 1 : 0]], WS[chans[nch > 2 ? 2 : 0]], x, ldx, U);
   if (f32) {
     AIM_ANTERP(float, c->d_at_wf)
@@ -1557,10 +1537,9 @@ static aim_status grid_pre(Ctx* c, const int* chans, int nch, int nrhs, const do
 #undef AIM_ANTERP
   }
   AIM_HIP_CHECK(hipGetLastError());
-  if (!t.tasks.empty()) return AIM_OK;   // the column pass reads U
   ProfScope ps(c, AIM_K_ROWS_FWD);
-  return launch_rows_fwd<T>(t.n, U, t.n_act, c->d_row_ptr, c->d_act_ix, t.nr, tile_rows(t.nr), nch * nrhs,
-                            (cplx<T>*)c->d_T, grid_twiddles<T>(c), s);
+  return launch_rows_fwd<T>(t.n, U, t.n_act, c->d_row_ptr, c->d_act_ix, t.nr, tile_rows(t.nr), pairs, Tb,
+                            grid_twiddles<T>(c), s);
 }
 
 template <typename T>
@@ -1581,7 +1560,7 @@ static aim_status grid_apply(Ctx* c, const int* chans, int nch, bool filt, int n
     // dispatch itself, so the interval is the kernel's own execution
     ProfScope ps(c, AIM_K_COLS, true);
     TRY(launch_cols<T>(t.n, 0, (cplx<T>*)c->d_T, t.nr, tile_rows(t.nr), nch * nrhs, grid_spectrum<T>(c, filt),
-                       grid_twiddles<T>(c), sparse_in(c), c->stream, ps.start(), ps.stop()));
+                       grid_twiddles<T>(c), c->stream, ps.start(), ps.stop()));
   }
   return grid_post<T>(c, nch, nrhs);
 }
@@ -1979,7 +1958,6 @@ aim_status matvec_pre(Ctx* c, int op, int nrhs, const double2* x, int64_t ldx, C
   job->pairs = nch * nrhs;
   job->f32 = f32;
   job->tiles = c->d_T;
-  job->in = sparse_in(c);
   if (f32) {
     job->Cq = grid_spectrum<float>(c, filt);
     job->tw = grid_twiddles<float>(c);
@@ -2003,42 +1981,34 @@ aim_status matvec_post(Ctx* c, int op, int nrhs, const double2* x, int64_t ldx, 
 }
 
 // One column pass over the tile sets of `count` jobs with the same spectrum,
-// twiddles, n and precision, in launches of up to kColBatchMax pairs; jobs
-// that bring transformed rows and jobs that bring active points (SparseIn)
-// go in separate launches.
+// twiddles, n and precision, in launches of up to ColBatch::kMax pairs.
 aim_status launch_cols_jobs(const ColsJob* jobs, int count, hipStream_t s) {
   if (count < 1) return AIM_OK;
   const int n = jobs[0].n;
   const bool f32 = jobs[0].f32;
   const int cb = col_block(n, f32);
   if (cb <= 0) return AIM_E_ARG;
-  for (const bool sparse : {false, true}) {
-    std::vector<void*> tiles;
-    std::vector<int> nr, ldt;
-    std::vector<SparseIn> in;
-    for (int i = 0; i < count; ++i) {
-      const ColsJob& j = jobs[i];
-      if (j.n != n || j.f32 != f32 || j.Cq != jobs[0].Cq) return AIM_E_ARG;
-      if ((j.in.nslot > 0) != sparse) continue;
-      const size_t b = f32 ? 8 : 16, pair_bytes = (size_t)(n / cb) * j.ldt * cb * b;
-      for (int p = 0; p < j.pairs; ++p) {
-        tiles.push_back((char*)j.tiles + p * pair_bytes);
-        nr.push_back(j.nr);
-        ldt.push_back(j.ldt);
-        in.push_back(j.in);
-        if (sparse) in.back().U = (const char*)j.in.U + (size_t)p * j.in.nslot * b;
-      }
+  std::vector<void*> tiles;
+  std::vector<int> nr, ldt;
+  for (int i = 0; i < count; ++i) {
+    const ColsJob& j = jobs[i];
+    if (j.n != n || j.f32 != f32 || j.Cq != jobs[0].Cq) return AIM_E_ARG;
+    const size_t pair_bytes = (size_t)(n / cb) * j.ldt * cb * (f32 ? 8 : 16);
+    for (int p = 0; p < j.pairs; ++p) {
+      tiles.push_back((char*)j.tiles + p * pair_bytes);
+      nr.push_back(j.nr);
+      ldt.push_back(j.ldt);
     }
-    const int total = (int)tiles.size();
-    for (int e0 = 0; e0 < total; e0 += kColBatchMax) {
-      const int cnt = std::min(kColBatchMax, total - e0);
-      if (f32)
-        TRY(launch_cols_group<float>(n, cnt, tiles.data() + e0, nr.data() + e0, ldt.data() + e0, in.data() + e0,
-                                     (const float2*)jobs[0].Cq, (const float2*)jobs[0].tw, s));
-      else
-        TRY(launch_cols_group<double>(n, cnt, tiles.data() + e0, nr.data() + e0, ldt.data() + e0, in.data() + e0,
-                                      (const double2*)jobs[0].Cq, (const double2*)jobs[0].tw, s));
-    }
+  }
+  const int total = (int)tiles.size();
+  for (int e0 = 0; e0 < total; e0 += kColBatchMax) {
+    const int cnt = std::min(kColBatchMax, total - e0);
+    if (f32)
+      TRY(launch_cols_group<float>(n, cnt, tiles.data() + e0, nr.data() + e0, ldt.data() + e0,
+                                   (const float2*)jobs[0].Cq, (const float2*)jobs[0].tw, s));
+    else
+      TRY(launch_cols_group<double>(n, cnt, tiles.data() + e0, nr.data() + e0, ldt.data() + e0,
+                                    (const double2*)jobs[0].Cq, (const double2*)jobs[0].tw, s));
   }
   return AIM_OK;
 }
