@@ -180,6 +180,7 @@ struct Ctx {
   int nch_max = 1;          // grid channels of the widest operator
   double alpha = 0;         // current filter cutoff (inf: none)
   bool filtered = false;
+  int kcut = 0;             // the filtered spectrum is zero past |kx| = kcut
   // geometry
   double *d_vx = nullptr, *d_vy = nullptr, *d_h = nullptr, *d_tx = nullptr, *d_ty = nullptr;
   double *d_glx = nullptr, *d_glw = nullptr;
@@ -267,6 +268,7 @@ struct ColsJob {
   const void* tw = nullptr;
   void* tiles = nullptr;
   int n = 0, nr = 0, ldt = 0, pairs = 0;
+  int kcut = 0;             // the spectrum is zero past |kx| = kcut
   bool f32 = false;
 };
 static constexpr int kColBatchMax = 32;   // tile sets per grouped column-pass launch

@@ -506,8 +506,10 @@ template <typename T, int N> struct ColCfg {
 // Column-pass block b -> tile tb and first column c0 within the tile.  The
 // K = CB / CW blocks of a tile are 8 apart, which the launch deals to the
 // same XCD, so the parts of each tile line meet in one L2.
-template <typename T, int N>
-__device__ __forceinline__ void col_block_of(int b, int& tb, int& c0) {
+// CUT: tiles past the first `keep` but the last are left out, block positions
+// keep .. hold the last tile, then nothing (false).
+template <typename T, int N, bool CUT>
+__device__ __forceinline__ bool col_block_of(int b, int keep, int& tb, int& c0) {
   constexpr int CB = ColCfg<T, N>::CB, CW = ColCfg<T, N>::CW, K = CB / CW;   // blocks per tile
   if constexpr (K == 1) {
     tb = b;
@@ -517,6 +519,15 @@ __device__ __forceinline__ void col_block_of(int b, int& tb, int& c0) {
     tb = (b / (8 * K)) * 8 + (b & 7);
     c0 = ((b >> 3) & (K - 1)) * CW;
   }
+  if constexpr (CUT) {
+    if (tb > keep) return false;
+    if (tb == keep) tb = N / CB - 1;
+  }
+  return true;
+}
+template <typename T, int N> int col_blocks(int keep) {
+  constexpr int K = ColCfg<T, N>::CB / ColCfg<T, N>::CW;
+  return K == 1 ? keep + 1 : (keep + 8) / 8 * 8 * K;
 }
 
 __device__ __forceinline__ void col_of(int b, int c, int N, int CB, int& kx, int& kxq) {
@@ -543,15 +554,26 @@ __device__ __forceinline__ int xcd_row(int bid, int nrows) {
 // kernels.  T layout (tiled): [pair][tile][row][CB] with ldt >= nr rows
 // per tile (tile_rows); rows nr .. ldt-1 are never read or written
 // ---------------------------------------------------------------------------
+// A filtered spectrum is zero past |kx| = kcut: its products take only the
+// tiles that hold a column up to kcut (the first `keep` ones, and the last
+// tile, which has column 0); the others are neither written nor read.
+template <int NBLK> __device__ __forceinline__ bool tile_kept(int tile, int keep) {
+  return tile < keep || tile == NBLK - 1;
+}
+template <int CB, int N> constexpr int tiles_kept(int kcut) {
+  const int t = (kcut + CB / 2 - 1) / (CB / 2);
+  return t < 1 ? 1 : (t > N / CB - 1 ? N / CB - 1 : t);
+}
+
 template <int N> constexpr int row_threads() { return N / 16 < 64 ? 64 : (N / 16 > 256 ? 256 : N / 16); }
 
 // Pass 1: gather active values of a row into a zeroed LDS row, FFT along x.
 // Active points have x < N/2, so only that half is cleared and the first pass
 // reads inputs 0..7 of its radix-16 butterflies.
-template <typename T, int N>
+template <typename T, int N, bool CUT>
 __global__ __launch_bounds__(row_threads<N>()) void k_rows_fwd(
     const cplx<T>* __restrict__ U, int n_act, const int32_t* __restrict__ row_ptr,
-    const int32_t* __restrict__ act_ix, int nr, int ldt, cplx<T>* __restrict__ Tb,
+    const int32_t* __restrict__ act_ix, int nr, int ldt, int keep, cplx<T>* __restrict__ Tb,
     const cplx<T>* __restrict__ tw) {
   using V = cplx<T>;
   static_assert(N >= 32, "row pass assumes at least two forward passes");
@@ -612,16 +634,17 @@ __global__ __launch_bounds__(row_threads<N>()) void k_rows_fwd(
 #pragma unroll
   for (int q = 0; q < PER; ++q) {
     const int idx = tid + q * NT;
-    if ((N % NT) == 0 || idx < N) out[(size_t)(idx / CB) * ldt * CB + idx % CB] = v[q];
+    if (((N % NT) == 0 || idx < N) && (!CUT || tile_kept<NBLK>(idx / CB, keep)))
+      out[(size_t)(idx / CB) * ldt * CB + idx % CB] = v[q];
   }
 }
 
 // Pass 3: inverse FFT along x, gather the active points of the row.  The
 // inverse runs its radices in reverse order so that the last pass is radix 16
 // and computes only the outputs x < N/2, where the active points lie.
-template <typename T, int N>
+template <typename T, int N, bool CUT>
 __global__ __launch_bounds__(row_threads<N>()) void k_rows_inv(
-    const cplx<T>* __restrict__ Tb, int nr, int ldt, const int32_t* __restrict__ row_ptr,
+    const cplx<T>* __restrict__ Tb, int nr, int ldt, int keep, const int32_t* __restrict__ row_ptr,
     const int32_t* __restrict__ act_ix, cplx<T>* __restrict__ Vout, int n_act,
     const cplx<T>* __restrict__ tw) {
   using V = cplx<T>;
@@ -653,7 +676,8 @@ __global__ __launch_bounds__(row_threads<N>()) void k_rows_inv(
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
       const int idx = tid + q * NT;
-      if ((N % NT) == 0 || idx < N) v[q] = in[(size_t)(idx / CB) * ldt * CB + idx % CB];
+      if ((N % NT) == 0 || idx < N)
+        v[q] = !CUT || tile_kept<NBLK>(idx / CB, keep) ? in[(size_t)(idx / CB) * ldt * CB + idx % CB] : mk<T>(0, 0);
     }
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
@@ -695,6 +719,138 @@ __global__ __launch_bounds__(row_threads<N>()) void k_rows_inv(
   const int a0 = row_ptr[row], a1 = row_ptr[row + 1];
   V* Vp = Vout + (size_t)pair * n_act;
   for (int a = a0 + tid; a < a1; a += NT) Vp[a] = buf[pidx(act_ix[a])];
+}
+
+// Row passes of a spectrum with few kept columns (pk pairs and column 0): the
+// active points of a row are few as well, so the kept columns are summed
+// point by point.  With T(k) and T(N - k) side by side one look-up of w =
+// W_N^{k x} serves both: forward u w and u conj(w); inverse, with P, M = T(k) +-
+// T(N - k), P cos + i M sin.  A block takes a row of RB pairs, which share the
+// look-ups; sums of a column do not depend on RB.  The other columns of the
+// last tile meet zero spectrum values.  Bound by the latency of short rows
+// (8 points on average), not by the sums: n = 2048, m = 600 contour of 252
+// pulses, 88 of 1024 pairs kept, 64 modes, FFTs of the kept tiles -> sums:
+// forward 170 -> 44 us, inverse 192 -> 53 us.
+static constexpr int kFewPairs = 4, kFewCols = 32;
+
+// One wave: kFewCols columns by two shares (odd and even) of the points.
+template <typename T, int N, int RB>
+__global__ __launch_bounds__(64) void k_rows_fwd_few(
+    const cplx<T>* __restrict__ U, int n_act, const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ act_ix,
+    int nr, int ldt, int pk, int pairs, cplx<T>* __restrict__ Tb, const cplx<T>* __restrict__ tw) {
+  using V = cplx<T>;
+  constexpr int CB = ColCfg<T, N>::CB, PC = 64;   // points staged at a time
+  __shared__ V us[RB][PC];
+  __shared__ int xs[PC];
+  const int row = xcd_row(blockIdx.x, nr), p0 = blockIdx.y * RB;
+  if (row >= nr) return;
+  const int a0 = row_ptr[row], a1 = row_ptr[row + 1], np = min(RB, pairs - p0);
+  const int k = blockIdx.z * kFewCols + (threadIdx.x & (kFewCols - 1)), g = threadIdx.x / kFewCols;
+  T a[4 * RB];   // per pair: sums of u.x w.x, u.y w.y, u.x w.y, u.y w.x
+#pragma unroll
+  for (int r = 0; r < 4 * RB; ++r) a[r] = 0;
+  for (int s0 = a0; s0 < a1; s0 += PC) {
+    const int cnt = min(PC, a1 - s0);
+    __syncthreads();
+    if ((int)threadIdx.x < cnt) {
+      xs[threadIdx.x] = act_ix[s0 + threadIdx.x];
+      for (int r = 0; r < np; ++r) us[r][threadIdx.x] = U[(size_t)(p0 + r) * n_act + s0 + threadIdx.x];
+    }
+    __syncthreads();
+#pragma unroll 4
+    for (int i = g; i < cnt; i += 2) {
+      const V w = tw[(k * xs[i]) & (N - 1)];
+#pragma unroll
+      for (int r = 0; r < RB; ++r) {
+        const V u = us[r][i];   // slots past np hold anything: their sums are dropped
+        a[4 * r] += u.x * w.x; a[4 * r + 1] += u.y * w.y; a[4 * r + 2] += u.x * w.y; a[4 * r + 3] += u.y * w.x;
+      }
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < 4 * RB; ++r) a[r] += __shfl_xor(a[r], kFewCols);
+  if (k > pk) return;
+#pragma unroll
+  for (int r = 0; r < RB; ++r) {
+    if (r >= np || (r & 1) != (RB == 1 ? 0 : g)) continue;   // each share writes every other pair
+    if (RB == 1 && g) continue;
+    V* row_out = Tb + ((size_t)(p0 + r) * (N / CB) * ldt + row) * CB;
+    V* o = k ? row_out + (size_t)((k - 1) / (CB / 2)) * ldt * CB + (k - 1) % (CB / 2) * 2
+             : row_out + (size_t)(N / CB - 1) * ldt * CB + CB - 2;
+    o[0] = mk<T>(a[4 * r] - a[4 * r + 1], a[4 * r + 2] + a[4 * r + 3]);
+    o[1] = k ? mk<T>(a[4 * r] + a[4 * r + 1], a[4 * r + 3] - a[4 * r + 2]) : mk<T>(0, 0);
+    if (k == 0)
+      for (int q = 2 - CB; q < 0; ++q) o[q] = mk<T>(0, 0);
+  }
+}
+
+// sums of v[0 .. NV-1] over the 16 lanes of a group, halving the set with the
+// lanes: v[0] of lane l holds sum number l / (16 / NV)
+template <int NV, typename T> __device__ __forceinline__ void few_sum(T (&v)[NV], int l) {
+#pragma unroll
+  for (int off = 8, n = NV; off >= 1; off >>= 1) {
+    if (n > 1) {
+      n >>= 1;
+      const bool hi = l & off;
+#pragma unroll
+      for (int i = 0; i < n; ++i) {
+        const T mine = hi ? v[i + n] : v[i], other = hi ? v[i] : v[i + n];
+        v[i] = mine + __shfl_xor(other, off, 16);
+      }
+    } else {
+      v[0] += __shfl_xor(v[0], off, 16);
+    }
+  }
+}
+
+template <int RB> constexpr int few_inv_threads() { return RB == 1 ? 512 : 256; }
+template <typename T, int N, int RB>
+__global__ __launch_bounds__(few_inv_threads<RB>()) void k_rows_inv_few(
+    const cplx<T>* __restrict__ Tb, int nr, int ldt, int pk, int pairs, const int32_t* __restrict__ row_ptr,
+    const int32_t* __restrict__ act_ix, cplx<T>* __restrict__ Vout, int n_act, const cplx<T>* __restrict__ tw) {
+  using V = cplx<T>;
+  constexpr int CB = ColCfg<T, N>::CB, NT = few_inv_threads<RB>();
+  extern __shared__ double2 few_lds[];
+  V* pm = (V*)few_lds;   // [r][k]: P, M (k = 0: T(0), 0)
+  const int row = xcd_row(blockIdx.x, nr), p0 = blockIdx.y * RB;
+  if (row >= nr) return;
+  const int np = min(RB, pairs - p0);
+  for (int i = threadIdx.x; i < np * (pk + 1); i += NT) {
+    const int r = i / (pk + 1), k = i % (pk + 1);
+    const V* in = Tb + ((size_t)(p0 + r) * (N / CB) * ldt + row) * CB;
+    if (k) {
+      in += (size_t)((k - 1) / (CB / 2)) * ldt * CB + (k - 1) % (CB / 2) * 2;
+      const V a = in[0], b = in[1];
+      pm[2 * i] = cadd(a, b);
+      pm[2 * i + 1] = csub(a, b);
+    } else {
+      pm[2 * i] = in[(size_t)(N / CB - 1) * ldt * CB + CB - 2];
+      pm[2 * i + 1] = mk<T>(0, 0);
+    }
+  }
+  __syncthreads();
+  const int a0 = row_ptr[row], a1 = row_ptr[row + 1], l = threadIdx.x & 15;
+  for (int a = a0 + (threadIdx.x >> 4); a < a1; a += NT / 16) {   // 16 lanes per point
+    const int x = act_ix[a];
+    T v[2 * RB];   // x, y parts per pair
+#pragma unroll
+    for (int r = 0; r < 2 * RB; ++r) v[r] = 0;
+#pragma unroll 1
+    for (int k = l; k <= pk; k += 16) {
+      const V w = tw[(k * x) & (N - 1)];   // cos, -sin
+#pragma unroll
+      for (int r = 0; r < RB; ++r) {
+        const V* q = pm + 2 * (size_t)((r < np ? r : 0) * (pk + 1) + k);
+        const V p = q[0], m = q[1];
+        v[2 * r] += p.x * w.x + m.y * w.y;
+        v[2 * r + 1] += p.y * w.x - m.x * w.y;
+      }
+    }
+    few_sum<2 * RB>(v, l);
+    constexpr int SL = 16 / (2 * RB);   // lanes that hold the same sum
+    if (l % SL == 0 && l / SL / 2 < np)
+      ((T*)(Vout + (size_t)(p0 + l / SL / 2) * n_act + a))[l / SL & 1] = v[0];
+  }
 }
 
 // Set-up: in-place forward FFT of full rows of length N (row-major array).
@@ -883,7 +1039,7 @@ __device__ __forceinline__ void cols_conv_tile(cplx<T>* buf, cplx<T>* __restrict
 
 template <typename T, int N, int MODE>
 __global__ __launch_bounds__((ColCfg<T, N>::NT)) void k_cols(
-    cplx<T>* __restrict__ Tb, int nr, int ldt, const cplx<T>* __restrict__ Cq,
+    cplx<T>* __restrict__ Tb, int nr, int ldt, int keep, const cplx<T>* __restrict__ Cq,
     const cplx<T>* __restrict__ tw) {
   using V = cplx<T>;
   constexpr int CB = ColCfg<T, N>::CB;
@@ -894,9 +1050,9 @@ __global__ __launch_bounds__((ColCfg<T, N>::NT)) void k_cols(
   const int b = blockIdx.x;
   const int pair = blockIdx.y;
   const int tid = threadIdx.x;
-  if constexpr (MODE == 0) {
+  if constexpr (MODE != 1) {
     int tb, c0;
-    col_block_of<T, N>(b, tb, c0);
+    if (!col_block_of<T, N, MODE == 2>(b, keep, tb, c0)) return;
     cols_conv_tile<T, N>(buf, Tb + ((size_t)pair * NBLK + tb) * ldt * CB, nr, tb, c0, Cq, tw);
   } else {
     const int kx0 = b * CW;
@@ -925,14 +1081,15 @@ struct ColBatch {
 };
 
 template <typename T, int N>
-__global__ __launch_bounds__((ColCfg<T, N>::NT)) void k_cols_group(ColBatch batch, const cplx<T>* __restrict__ Cq,
+__global__ __launch_bounds__((ColCfg<T, N>::NT)) void k_cols_group(ColBatch batch, int keep,
+                                                                 const cplx<T>* __restrict__ Cq,
                                                                  const cplx<T>* __restrict__ tw) {
   using V = cplx<T>;
   constexpr int CB = ColCfg<T, N>::CB;
   __shared__ V buf[padded(N * ColCfg<T, N>::CW)];
   const int e = blockIdx.y;
   int tb, c0;
-  col_block_of<T, N>(blockIdx.x, tb, c0);
+  if (!col_block_of<T, N, true>(blockIdx.x, keep, tb, c0)) return;
   V* tile = (V*)batch.tile[e] + (size_t)tb * batch.ldt[e] * CB;
   cols_conv_tile<T, N>(buf, tile, batch.nr[e], tb, c0, Cq, tw);
 }
@@ -942,18 +1099,71 @@ __global__ __launch_bounds__((ColCfg<T, N>::NT)) void k_cols_group(ColBatch batc
 // ---------------------------------------------------------------------------
 #define AIM_FOR_SIZES(X) X(32) X(64) X(128) X(256) X(512) X(1024) X(2048) X(4096)
 
+// Row passes over the tiles a spectrum cut at kcut keeps: sums over the kept
+// columns where these cost less than FFTs of the rows.  The sums take pk n_act
+// steps, the FFTs nr N (log); whole products, FFTs / sums in us, for one
+// right-hand side and a batch, by pk n_act / (nr N):
+//   n = 2048:  .35  25.7 / 22.0, 237 / 129    .52  26.6 / 23.8, 256 / 159
+//              .65  30.4 / 30.4, 113 / 86     .98  31.2 / 34.8, 120 / 104
+//   n = 1024:  .47  22.9 / 22.1,  60 / 53     .94  23.3 / 23.2,  66 / 63
+// Below n = 512 the FFTs are as short as a row's sums (n = 128: 36 / 39).  Past
+// N / 16 pairs (LDS of the inverse sums) no contour meets the rule.
+template <typename T, int N>
+bool rows_few(int kcut, int n_act, int nr, int& pk) {
+  pk = tiles_kept<ColCfg<T, N>::CB, N>(kcut) * (ColCfg<T, N>::CB / 2);
+  return N >= 512 && pk <= N / 16 && 5 * (int64_t)pk * n_act <= 3 * (int64_t)N * nr;
+}
+template <typename T, int N>
+void rows_fwd(const cplx<T>* U, int n_act, const int32_t* row_ptr, const int32_t* act_ix, int nr, int ldt, int kcut,
+              int pairs, cplx<T>* Tb, const cplx<T>* tw, hipStream_t s) {
+  const unsigned rows = 8 * ((nr + 7) / 8);
+  const dim3 g(rows, pairs), b(row_threads<N>());
+  const int keep = tiles_kept<ColCfg<T, N>::CB, N>(kcut);
+  int pk;
+  if (rows_few<T, N>(kcut, n_act, nr, pk)) {
+    const int kc = pk / kFewCols + 1;
+    if (pairs < kFewPairs)
+      hipLaunchKernelGGL((k_rows_fwd_few<T, N, 1>), dim3(rows, pairs, kc), dim3(64), 0, s, U, n_act, row_ptr, act_ix, nr, ldt, pk,
+                         pairs, Tb, tw);
+    else
+      hipLaunchKernelGGL((k_rows_fwd_few<T, N, kFewPairs>), dim3(rows, (pairs + kFewPairs - 1) / kFewPairs, kc),
+                         dim3(64), 0, s, U, n_act, row_ptr, act_ix, nr, ldt, pk, pairs, Tb, tw);
+  } else if (keep == N / ColCfg<T, N>::CB - 1) {
+    hipLaunchKernelGGL((k_rows_fwd<T, N, false>), g, b, 0, s, U, n_act, row_ptr, act_ix, nr, ldt, keep, Tb, tw);
+  } else {
+    hipLaunchKernelGGL((k_rows_fwd<T, N, true>), g, b, 0, s, U, n_act, row_ptr, act_ix, nr, ldt, keep, Tb, tw);
+  }
+}
+template <typename T, int N>
+void rows_inv(const cplx<T>* Tb, int nr, int ldt, int kcut, const int32_t* row_ptr, const int32_t* act_ix, int pairs,
+              cplx<T>* V, int n_act, const cplx<T>* tw, hipStream_t s) {
+  const unsigned rows = 8 * ((nr + 7) / 8);
+  const dim3 g(rows, pairs), b(row_threads<N>());
+  const int keep = tiles_kept<ColCfg<T, N>::CB, N>(kcut);
+  int pk;
+  if (rows_few<T, N>(kcut, n_act, nr, pk)) {
+    const size_t lds = 2 * (size_t)(pk + 1) * sizeof(cplx<T>);
+    if (pairs < kFewPairs)
+      hipLaunchKernelGGL((k_rows_inv_few<T, N, 1>), g, dim3(few_inv_threads<1>()), lds, s, Tb, nr, ldt, pk, pairs, row_ptr,
+                         act_ix, V, n_act, tw);
+    else
+      hipLaunchKernelGGL((k_rows_inv_few<T, N, kFewPairs>), dim3(rows, (pairs + kFewPairs - 1) / kFewPairs),
+                         dim3(few_inv_threads<kFewPairs>()), kFewPairs * lds, s, Tb, nr, ldt, pk, pairs, row_ptr, act_ix, V, n_act, tw);
+  } else if (keep == N / ColCfg<T, N>::CB - 1) {
+    hipLaunchKernelGGL((k_rows_inv<T, N, false>), g, b, 0, s, Tb, nr, ldt, keep, row_ptr, act_ix, V, n_act, tw);
+  } else {
+    hipLaunchKernelGGL((k_rows_inv<T, N, true>), g, b, 0, s, Tb, nr, ldt, keep, row_ptr, act_ix, V, n_act, tw);
+  }
+}
+
 template <typename T>
 aim_status launch_rows_fwd(int n, const cplx<T>* U, int n_act, const int32_t* row_ptr,
-                           const int32_t* act_ix, int nr, int ldt, int pairs, cplx<T>* Tb,
+                           const int32_t* act_ix, int nr, int ldt, int kcut, int pairs, cplx<T>* Tb,
                            const cplx<T>* tw, hipStream_t s) {
   if (ldt < nr) return AIM_E_ARG;
-  dim3 g(8 * ((nr + 7) / 8), pairs);
   switch (n) {
-#define CASE(NN)                                                                               \
-  case NN:                                                                                     \
-    hipLaunchKernelGGL((k_rows_fwd<T, NN>), g, dim3(row_threads<NN>()), 0, s, U, n_act, row_ptr, \
-                       act_ix, nr, ldt, Tb, tw);                                               \
-    break;
+#define CASE(NN) \
+  case NN: rows_fwd<T, NN>(U, n_act, row_ptr, act_ix, nr, ldt, kcut, pairs, Tb, tw, s); break;
     AIM_FOR_SIZES(CASE)
 #undef CASE
     default: return AIM_E_ARG;
@@ -962,17 +1172,13 @@ aim_status launch_rows_fwd(int n, const cplx<T>* U, int n_act, const int32_t* ro
 }
 
 template <typename T>
-aim_status launch_rows_inv(int n, const cplx<T>* Tb, int nr, int ldt, const int32_t* row_ptr,
+aim_status launch_rows_inv(int n, const cplx<T>* Tb, int nr, int ldt, int kcut, const int32_t* row_ptr,
                            const int32_t* act_ix, int pairs, cplx<T>* V, int n_act,
                            const cplx<T>* tw, hipStream_t s) {
   if (ldt < nr) return AIM_E_ARG;
-  dim3 g(8 * ((nr + 7) / 8), pairs);
   switch (n) {
-#define CASE(NN)                                                                               \
-  case NN:                                                                                     \
-    hipLaunchKernelGGL((k_rows_inv<T, NN>), g, dim3(row_threads<NN>()), 0, s, Tb, nr, ldt,      \
-                       row_ptr, act_ix, V, n_act, tw);                                         \
-    break;
+#define CASE(NN) \
+  case NN: rows_inv<T, NN>(Tb, nr, ldt, kcut, row_ptr, act_ix, pairs, V, n_act, tw, s); break;
     AIM_FOR_SIZES(CASE)
 #undef CASE
     default: return AIM_E_ARG;
@@ -981,20 +1187,22 @@ aim_status launch_rows_inv(int n, const cplx<T>* Tb, int nr, int ldt, const int3
 }
 
 template <typename T>
-aim_status launch_cols(int n, int mode, cplx<T>* Tb, int nr, int ldt, int pairs, const cplx<T>* Cq,
+aim_status launch_cols(int n, int mode, cplx<T>* Tb, int nr, int ldt, int kcut, int pairs, const cplx<T>* Cq,
                        const cplx<T>* tw, hipStream_t s, hipEvent_t ev_start, hipEvent_t ev_stop) {
   // kept rows lie in the unpadded half
   if (mode == 0 && (nr < 1 || nr > n / 2 || ldt < nr)) return AIM_E_ARG;
   switch (n) {
-#define CASE(NN)                                                                          \
-  case NN: {                                                                              \
-    dim3 g(NN / ColCfg<T, NN>::CW, pairs);                                                \
-    if (mode == 0)                                                                        \
-      hipExtLaunchKernelGGL((k_cols<T, NN, 0>), g, dim3(ColCfg<T, NN>::NT), 0, s, ev_start, ev_stop, 0, \
-                            Tb, nr, ldt, Cq, tw);                                         \
-    else                                                                                  \
-      hipLaunchKernelGGL((k_cols<T, NN, 1>), g, dim3(ColCfg<T, NN>::NT), 0, s, Tb, nr, ldt, Cq, tw); \
-    break;                                                                                \
+#define CASE(NN)                                                                                                     \
+  case NN: {                                                                                                         \
+    const int keep = tiles_kept<ColCfg<T, NN>::CB, NN>(kcut);                                                        \
+    const dim3 g(col_blocks<T, NN>(keep), pairs), b(ColCfg<T, NN>::NT);                                              \
+    if (mode != 0)                                                                                                   \
+      hipLaunchKernelGGL((k_cols<T, NN, 1>), dim3(NN / ColCfg<T, NN>::CW, pairs), b, 0, s, Tb, nr, ldt, 0, Cq, tw);  \
+    else if (keep == NN / ColCfg<T, NN>::CB - 1)                                                                     \
+      hipExtLaunchKernelGGL((k_cols<T, NN, 0>), g, b, 0, s, ev_start, ev_stop, 0, Tb, nr, ldt, keep, Cq, tw);        \
+    else                                                                                                             \
+      hipExtLaunchKernelGGL((k_cols<T, NN, 2>), g, b, 0, s, ev_start, ev_stop, 0, Tb, nr, ldt, keep, Cq, tw);        \
+    break;                                                                                                           \
   }
     AIM_FOR_SIZES(CASE)
 #undef CASE
@@ -1016,7 +1224,7 @@ int col_block(int n, bool f32) {
 
 // grouped column pass over `count` tile sets (count <= ColBatch::kMax)
 template <typename T>
-aim_status launch_cols_group(int n, int count, void* const* tiles, const int* nr, const int* ldt,
+aim_status launch_cols_group(int n, int count, void* const* tiles, const int* nr, const int* ldt, int kcut,
                              const cplx<T>* Cq, const cplx<T>* tw, hipStream_t s) {
   if (count < 1 || count > ColBatch::kMax) return AIM_E_ARG;
   ColBatch bt;
@@ -1030,8 +1238,11 @@ aim_status launch_cols_group(int n, int count, void* const* tiles, const int* nr
   switch (n) {
 #define CASE(NN)                                                                                              \
   case NN:                                                                                                    \
-    hipLaunchKernelGGL((k_cols_group<T, NN>), dim3(NN / ColCfg<T, NN>::CW, count), dim3(ColCfg<T, NN>::NT), 0, \
-                       s, bt, Cq, tw);                                                                        \
+    {                                                                                                         \
+      const int keep = tiles_kept<ColCfg<T, NN>::CB, NN>(kcut);                                               \
+      hipLaunchKernelGGL((k_cols_group<T, NN>), dim3(col_blocks<T, NN>(keep), count), dim3(ColCfg<T, NN>::NT), 0, s, bt, \
+                         keep, Cq, tw);                                                                       \
+    }                                                                                                         \
     break;
     AIM_FOR_SIZES(CASE)
 #undef CASE
@@ -1053,21 +1264,21 @@ aim_status launch_rows_fft_inplace(int n, double2* A, const double2* tw, hipStre
   return hipGetLastError() == hipSuccess ? AIM_OK : AIM_E_HIP;
 }
 
-template aim_status launch_rows_fwd<double>(int, const double2*, int, const int32_t*, const int32_t*, int, int, int,
+template aim_status launch_rows_fwd<double>(int, const double2*, int, const int32_t*, const int32_t*, int, int, int, int,
                                             double2*, const double2*, hipStream_t);
-template aim_status launch_rows_fwd<float>(int, const float2*, int, const int32_t*, const int32_t*, int, int, int,
+template aim_status launch_rows_fwd<float>(int, const float2*, int, const int32_t*, const int32_t*, int, int, int, int,
                                            float2*, const float2*, hipStream_t);
-template aim_status launch_rows_inv<double>(int, const double2*, int, int, const int32_t*, const int32_t*, int,
+template aim_status launch_rows_inv<double>(int, const double2*, int, int, int, const int32_t*, const int32_t*, int,
                                             double2*, int, const double2*, hipStream_t);
-template aim_status launch_rows_inv<float>(int, const float2*, int, int, const int32_t*, const int32_t*, int,
+template aim_status launch_rows_inv<float>(int, const float2*, int, int, int, const int32_t*, const int32_t*, int,
                                            float2*, int, const float2*, hipStream_t);
-template aim_status launch_cols<double>(int, int, double2*, int, int, int, const double2*, const double2*,
+template aim_status launch_cols<double>(int, int, double2*, int, int, int, int, const double2*, const double2*,
                                         hipStream_t, hipEvent_t, hipEvent_t);
-template aim_status launch_cols<float>(int, int, float2*, int, int, int, const float2*, const float2*, hipStream_t,
-                                       hipEvent_t, hipEvent_t);
-template aim_status launch_cols_group<double>(int, int, void* const*, const int*, const int*, const double2*,
+template aim_status launch_cols<float>(int, int, float2*, int, int, int, int, const float2*, const float2*,
+                                       hipStream_t, hipEvent_t, hipEvent_t);
+template aim_status launch_cols_group<double>(int, int, void* const*, const int*, const int*, int, const double2*,
                                               const double2*, hipStream_t);
-template aim_status launch_cols_group<float>(int, int, void* const*, const int*, const int*, const float2*,
+template aim_status launch_cols_group<float>(int, int, void* const*, const int*, const int*, int, const float2*,
                                              const float2*, hipStream_t);
 
 }  // namespace aim

@@ -21,19 +21,19 @@ namespace aim {
 
 template <typename T>
 aim_status launch_rows_fwd(int n, const cplx<T>* U, int n_act, const int32_t* row_ptr,
-                           const int32_t* act_ix, int nr, int ldt, int pairs, cplx<T>* Tb,
+                           const int32_t* act_ix, int nr, int ldt, int kcut, int pairs, cplx<T>* Tb,
                            const cplx<T>* tw, hipStream_t s);
 template <typename T>
-aim_status launch_rows_inv(int n, const cplx<T>* Tb, int nr, int ldt, const int32_t* row_ptr,
+aim_status launch_rows_inv(int n, const cplx<T>* Tb, int nr, int ldt, int kcut, const int32_t* row_ptr,
                            const int32_t* act_ix, int pairs, cplx<T>* V, int n_act,
                            const cplx<T>* tw, hipStream_t s);
 template <typename T>
-aim_status launch_cols(int n, int mode, cplx<T>* Tb, int nr, int ldt, int pairs, const cplx<T>* Cq,
+aim_status launch_cols(int n, int mode, cplx<T>* Tb, int nr, int ldt, int kcut, int pairs, const cplx<T>* Cq,
                        const cplx<T>* tw, hipStream_t s, hipEvent_t ev_start = nullptr,
                        hipEvent_t ev_stop = nullptr);
 aim_status launch_rows_fft_inplace(int n, double2* A, const double2* tw, hipStream_t s);
 template <typename T>
-aim_status launch_cols_group(int n, int count, void* const* tiles, const int* nr, const int* ldt,
+aim_status launch_cols_group(int n, int count, void* const* tiles, const int* nr, const int* ldt, int kcut,
                              const cplx<T>* Cq, const cplx<T>* tw, hipStream_t s);
 int col_block(int n, bool f32);
 
@@ -1207,7 +1207,7 @@ aim_status acquire_spectrum(Ctx* c, double keps) {
   }
   hipLaunchKernelGGL(k_sample_kernel, dim3((n + 255) / 256, n), dim3(256), 0, s, m, n, keps, cfull);
   aim_status st = launch_rows_fft_inplace(n, cfull, c->d_tw, s);
-  if (st == AIM_OK) st = launch_cols<double>(n, 1, cfull, n, n, 1, nullptr, c->d_tw, s);
+  if (st == AIM_OK) st = launch_cols<double>(n, 1, cfull, n, n, n / 2, 1, nullptr, c->d_tw, s);
   if (st == AIM_OK) {
     hipLaunchKernelGGL(k_extract_spectrum, dim3((spec_row_len(n) + 255) / 256, H), dim3(256), 0, s, n, cfull, e->C, e->Cf);
     if (hipStreamSynchronize(s) != hipSuccess) st = AIM_E_HIP;
@@ -1428,6 +1428,7 @@ aim_status setup_device(Ctx* c) {
 aim_status apply_filter(Ctx* c, double alpha) {
   const int n = c->t.n, H = n / 2 + 1;
   const bool all = !std::isfinite(alpha);
+  int kcut = n / 2;
   if (all) {   // no truncation: the filtered operator uses the shared spectrum
     c->d_Ca = c->d_C;
     c->d_Caf = c->d_Cf;
@@ -1437,12 +1438,15 @@ aim_status apply_filter(Ctx* c, double alpha) {
       if (c->precision == AIM_MIXED) TRY(dev_alloc(c, (void**)&c->own_Caf, (size_t)H * spec_row_len(n) * sizeof(float2)));
     }
     const double thr = ((alpha * n) * c->t.eps / (2.0 * kPi)) * ((alpha * n) * c->t.eps / (2.0 * kPi));
+    // the largest |kx| the mask keeps (at ky = 0)
+    while (kcut > 0 && !((double)kcut * kcut <= thr)) --kcut;
     hipLaunchKernelGGL(k_filter, dim3((spec_row_len(n) + 255) / 256, H), dim3(256), 0, c->stream, n, thr, false, c->d_C,
                        c->own_Ca, c->own_Caf);
     AIM_HIP_CHECK(hipGetLastError());
     c->d_Ca = c->own_Ca;
     c->d_Caf = c->own_Caf;
   }
+  c->kcut = kcut;
   c->alpha = alpha;
   c->filtered = !all;
   return AIM_OK;
@@ -1477,7 +1481,7 @@ aim_status apply_filter_analytic(Ctx* c, double alpha) {
     st = hipGetLastError() == hipSuccess ? AIM_OK : AIM_E_HIP;
   }
   if (st == AIM_OK) st = launch_rows_fft_inplace(n, cfull, c->d_tw, s);
-  if (st == AIM_OK) st = launch_cols<double>(n, 1, cfull, n, n, 1, nullptr, c->d_tw, s);
+  if (st == AIM_OK) st = launch_cols<double>(n, 1, cfull, n, n, n / 2, 1, nullptr, c->d_tw, s);
   if (st == AIM_OK) {
     hipLaunchKernelGGL(k_extract_spectrum, dim3((spec_row_len(n) + 255) / 256, H), dim3(256), 0, s, n, cfull, c->own_Ca,
                        c->own_Caf);
@@ -1489,6 +1493,7 @@ aim_status apply_filter_analytic(Ctx* c, double alpha) {
   if (st != AIM_OK) return st;
   c->d_Ca = c->own_Ca;
   c->d_Caf = c->own_Caf;
+  c->kcut = n / 2;
   c->alpha = alpha;
   c->filtered = true;
   return AIM_OK;
@@ -1509,8 +1514,11 @@ static const cplx<T>* grid_twiddles(Ctx* c) {
   return sizeof(T) == 4 ? (const cplx<T>*)c->d_twf : (const cplx<T>*)c->d_tw;
 }
 
+// the grid spectrum of a product is zero past this |kx|
+static int grid_kcut(const Ctx* c, bool filt) { return filt ? c->kcut : c->t.n / 2; }
+
 template <typename T>
-static aim_status grid_pre(Ctx* c, const int* chans, int nch, int nrhs, const double2* x, int64_t ldx) {
+static aim_status grid_pre(Ctx* c, const int* chans, int nch, bool filt, int nrhs, const double2* x, int64_t ldx) {
   HostTables& t = c->t;
   hipStream_t s = c->stream;
   const int pairs = nch * nrhs;
@@ -1538,31 +1546,31 @@ static aim_status grid_pre(Ctx* c, const int* chans, int nch, int nrhs, const do
   }
   AIM_HIP_CHECK(hipGetLastError());
   ProfScope ps(c, AIM_K_ROWS_FWD);
-  return launch_rows_fwd<T>(t.n, U, t.n_act, c->d_row_ptr, c->d_act_ix, t.nr, tile_rows(t.nr), pairs, Tb,
-                            grid_twiddles<T>(c), s);
+  return launch_rows_fwd<T>(t.n, U, t.n_act, c->d_row_ptr, c->d_act_ix, t.nr, tile_rows(t.nr), grid_kcut(c, filt),
+                            pairs, Tb, grid_twiddles<T>(c), s);
 }
 
 template <typename T>
-static aim_status grid_post(Ctx* c, int nch, int nrhs) {
+static aim_status grid_post(Ctx* c, int nch, bool filt, int nrhs) {
   HostTables& t = c->t;
   ProfScope ps(c, AIM_K_ROWS_INV);
-  return launch_rows_inv<T>(t.n, (cplx<T>*)c->d_T, t.nr, tile_rows(t.nr), c->d_row_ptr, c->d_act_ix, nch * nrhs,
-                            (cplx<T>*)c->d_V, t.n_act, grid_twiddles<T>(c), c->stream);
+  return launch_rows_inv<T>(t.n, (cplx<T>*)c->d_T, t.nr, tile_rows(t.nr), grid_kcut(c, filt), c->d_row_ptr, c->d_act_ix,
+                            nch * nrhs, (cplx<T>*)c->d_V, t.n_act, grid_twiddles<T>(c), c->stream);
 }
 
 template <typename T>
 static aim_status grid_apply(Ctx* c, const int* chans, int nch, bool filt, int nrhs, const double2* x,
                              int64_t ldx) {
   HostTables& t = c->t;
-  TRY(grid_pre<T>(c, chans, nch, nrhs, x, ldx));
+  TRY(grid_pre<T>(c, chans, nch, filt, nrhs, x, ldx));
   {
     // the dominant kernel's sampled launches carry their events in the
     // dispatch itself, so the interval is the kernel's own execution
     ProfScope ps(c, AIM_K_COLS, true);
-    TRY(launch_cols<T>(t.n, 0, (cplx<T>*)c->d_T, t.nr, tile_rows(t.nr), nch * nrhs, grid_spectrum<T>(c, filt),
-                       grid_twiddles<T>(c), c->stream, ps.start(), ps.stop()));
+    TRY(launch_cols<T>(t.n, 0, (cplx<T>*)c->d_T, t.nr, tile_rows(t.nr), grid_kcut(c, filt), nch * nrhs,
+                       grid_spectrum<T>(c, filt), grid_twiddles<T>(c), c->stream, ps.start(), ps.stop()));
   }
-  return grid_post<T>(c, nch, nrhs);
+  return grid_post<T>(c, nch, filt, nrhs);
 }
 
 template <typename T, int LANES>
@@ -1958,14 +1966,15 @@ aim_status matvec_pre(Ctx* c, int op, int nrhs, const double2* x, int64_t ldx, C
   job->pairs = nch * nrhs;
   job->f32 = f32;
   job->tiles = c->d_T;
+  job->kcut = grid_kcut(c, filt);
   if (f32) {
     job->Cq = grid_spectrum<float>(c, filt);
     job->tw = grid_twiddles<float>(c);
-    return grid_pre<float>(c, ch, nch, nrhs, x, ldx);
+    return grid_pre<float>(c, ch, nch, filt, nrhs, x, ldx);
   }
   job->Cq = grid_spectrum<double>(c, filt);
   job->tw = grid_twiddles<double>(c);
-  return grid_pre<double>(c, ch, nch, nrhs, x, ldx);
+  return grid_pre<double>(c, ch, nch, filt, nrhs, x, ldx);
 }
 
 aim_status matvec_post(Ctx* c, int op, int nrhs, const double2* x, int64_t ldx, double2* y, int64_t ldy) {
@@ -1973,10 +1982,10 @@ aim_status matvec_post(Ctx* c, int op, int nrhs, const double2* x, int64_t ldx, 
   if (!split_parts(c, op, &ch, &nch, &filt, &near, &sg, &sc)) return AIM_E_ARG;
   const double2* Cn = near ? (nch == 1 ? c->d_CS : c->d_CN) : nullptr;
   if (op & AIM_OP_GRID_FP32) {
-    TRY(grid_post<float>(c, nch, nrhs));
+    TRY(grid_post<float>(c, nch, filt, nrhs));
     return interp<float>(c, ch, nch, sg, near, Cn, nrhs, x, ldx, y, ldy, sc);
   }
-  TRY(grid_post<double>(c, nch, nrhs));
+  TRY(grid_post<double>(c, nch, filt, nrhs));
   return interp<double>(c, ch, nch, sg, near, Cn, nrhs, x, ldx, y, ldy, sc);
 }
 
@@ -1992,7 +2001,7 @@ aim_status launch_cols_jobs(const ColsJob* jobs, int count, hipStream_t s) {
   std::vector<int> nr, ldt;
   for (int i = 0; i < count; ++i) {
     const ColsJob& j = jobs[i];
-    if (j.n != n || j.f32 != f32 || j.Cq != jobs[0].Cq) return AIM_E_ARG;
+    if (j.n != n || j.f32 != f32 || j.Cq != jobs[0].Cq || j.kcut != jobs[0].kcut) return AIM_E_ARG;
     const size_t pair_bytes = (size_t)(n / cb) * j.ldt * cb * (f32 ? 8 : 16);
     for (int p = 0; p < j.pairs; ++p) {
       tiles.push_back((char*)j.tiles + p * pair_bytes);
@@ -2004,10 +2013,10 @@ aim_status launch_cols_jobs(const ColsJob* jobs, int count, hipStream_t s) {
   for (int e0 = 0; e0 < total; e0 += kColBatchMax) {
     const int cnt = std::min(kColBatchMax, total - e0);
     if (f32)
-      TRY(launch_cols_group<float>(n, cnt, tiles.data() + e0, nr.data() + e0, ldt.data() + e0,
+      TRY(launch_cols_group<float>(n, cnt, tiles.data() + e0, nr.data() + e0, ldt.data() + e0, jobs[0].kcut,
                                    (const float2*)jobs[0].Cq, (const float2*)jobs[0].tw, s));
     else
-      TRY(launch_cols_group<double>(n, cnt, tiles.data() + e0, nr.data() + e0, ldt.data() + e0,
+      TRY(launch_cols_group<double>(n, cnt, tiles.data() + e0, nr.data() + e0, ldt.data() + e0, jobs[0].kcut,
                                     (const double2*)jobs[0].Cq, (const double2*)jobs[0].tw, s));
   }
   return AIM_OK;
