@@ -506,9 +506,9 @@ template <typename T, int N> struct ColCfg {
 // Column-pass block b -> tile tb and first column c0 within the tile.  The
 // K = CB / CW blocks of a tile are 8 apart, which the launch deals to the
 // same XCD, so the parts of each tile line meet in one L2.
-// CUT: tiles past the first `keep` but the last are left out, block positions
-// keep .. hold the last tile, then nothing (false).
-template <typename T, int N, bool CUT>
+// Tiles past the first `keep` but the last are left out: block positions keep
+// .. hold the last tile, then nothing (false).
+template <typename T, int N>
 __device__ __forceinline__ bool col_block_of(int b, int keep, int& tb, int& c0) {
   constexpr int CB = ColCfg<T, N>::CB, CW = ColCfg<T, N>::CW, K = CB / CW;   // blocks per tile
   if constexpr (K == 1) {
@@ -519,10 +519,8 @@ __device__ __forceinline__ bool col_block_of(int b, int keep, int& tb, int& c0) 
     tb = (b / (8 * K)) * 8 + (b & 7);
     c0 = ((b >> 3) & (K - 1)) * CW;
   }
-  if constexpr (CUT) {
-    if (tb > keep) return false;
-    if (tb == keep) tb = N / CB - 1;
-  }
+  if (tb > keep) return false;
+  if (tb == keep) tb = N / CB - 1;
   return true;
 }
 template <typename T, int N> int col_blocks(int keep) {
@@ -1050,9 +1048,9 @@ __global__ __launch_bounds__((ColCfg<T, N>::NT)) void k_cols(
   const int b = blockIdx.x;
   const int pair = blockIdx.y;
   const int tid = threadIdx.x;
-  if constexpr (MODE != 1) {
+  if constexpr (MODE == 0) {
     int tb, c0;
-    if (!col_block_of<T, N, MODE == 2>(b, keep, tb, c0)) return;
+    if (!col_block_of<T, N>(b, keep, tb, c0)) return;
     cols_conv_tile<T, N>(buf, Tb + ((size_t)pair * NBLK + tb) * ldt * CB, nr, tb, c0, Cq, tw);
   } else {
     const int kx0 = b * CW;
@@ -1089,7 +1087,7 @@ __global__ __launch_bounds__((ColCfg<T, N>::NT)) void k_cols_group(ColBatch batc
   __shared__ V buf[padded(N * ColCfg<T, N>::CW)];
   const int e = blockIdx.y;
   int tb, c0;
-  if (!col_block_of<T, N, true>(blockIdx.x, keep, tb, c0)) return;
+  if (!col_block_of<T, N>(blockIdx.x, keep, tb, c0)) return;
   V* tile = (V*)batch.tile[e] + (size_t)tb * batch.ldt[e] * CB;
   cols_conv_tile<T, N>(buf, tile, batch.nr[e], tb, c0, Cq, tw);
 }
@@ -1198,10 +1196,8 @@ aim_status launch_cols(int n, int mode, cplx<T>* Tb, int nr, int ldt, int kcut, 
     const dim3 g(col_blocks<T, NN>(keep), pairs), b(ColCfg<T, NN>::NT);                                              \
     if (mode != 0)                                                                                                   \
       hipLaunchKernelGGL((k_cols<T, NN, 1>), dim3(NN / ColCfg<T, NN>::CW, pairs), b, 0, s, Tb, nr, ldt, 0, Cq, tw);  \
-    else if (keep == NN / ColCfg<T, NN>::CB - 1)                                                                     \
-      hipExtLaunchKernelGGL((k_cols<T, NN, 0>), g, b, 0, s, ev_start, ev_stop, 0, Tb, nr, ldt, keep, Cq, tw);        \
     else                                                                                                             \
-      hipExtLaunchKernelGGL((k_cols<T, NN, 2>), g, b, 0, s, ev_start, ev_stop, 0, Tb, nr, ldt, keep, Cq, tw);        \
+      hipExtLaunchKernelGGL((k_cols<T, NN, 0>), g, b, 0, s, ev_start, ev_stop, 0, Tb, nr, ldt, keep, Cq, tw);        \
     break;                                                                                                           \
   }
     AIM_FOR_SIZES(CASE)
