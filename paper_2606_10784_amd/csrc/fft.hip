@@ -424,9 +424,16 @@ __device__ __forceinline__ void ct_pass(cplx<T>* buf, const cplx<T>* __restrict_
   __syncthreads();
 }
 
+// LDS values that the lanes of one wave exchange: order, no barrier
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // ct_pass with the base twiddle of each of the thread's butterflies given
 // (w[q] for butterfly tid + q NT, forward sign)
-template <typename T, int N, int NCOL, int NT, bool INV, int S, int R>
+template <typename T, int N, int NCOL, int NT, bool INV, int S, int R, bool WAVE>
 __device__ __forceinline__ void ct_pass_w(cplx<T>* buf, const cplx<T>* w) {
   using V = cplx<T>;
   constexpr int NB = (N / R) * NCOL;
@@ -451,7 +458,8 @@ __device__ __forceinline__ void ct_pass_w(cplx<T>* buf, const cplx<T>* w) {
       for (int r = 0; r < R; ++r) buf[cidx<T>((base + S * r) * NCOL + c)] = v[r];
     }
   }
-  __syncthreads();
+  if constexpr (WAVE) wave_sync();
+  else __syncthreads();
 }
 
 // radix-16 forward passes with strides S, S/16, ... down to SEND (inclusive)
@@ -893,6 +901,8 @@ __device__ __forceinline__ void cols_conv_tile(cplx<T>* buf, cplx<T>* __restrict
   constexpr int NB1 = S1 * CW, PER1 = (NB1 + NT - 1) / NT;
   constexpr int NBM = (N / 16) * CW, PERM = (NBM + NT - 1) / NT;
   constexpr int NG = N / RL, NBF = NG * CW, PERF = (NBF + NT - 1) / NT;
+  // the last passes' groups of a wave are the positions of its middle passes
+  constexpr bool LOCAL = MID && NT == 256 && NB1 == 256 && NBF == 256 * PERF;
   // forward pass 1 (stride N/16, radix 16) from HBM: inputs m + S1 r with
   // r >= 8 lie in the zero half
   V v[PER1][16];
@@ -983,7 +993,7 @@ __device__ __forceinline__ void cols_conv_tile(cplx<T>* buf, cplx<T>* __restrict
     }
   }
   __syncthreads();
-  if constexpr (MID) ct_pass_w<T, N, CW, NT, false, SM, 16>(buf, wm);
+  if constexpr (MID) ct_pass_w<T, N, CW, NT, false, SM, 16, LOCAL>(buf, wm);
   if constexpr (LATE) {
 #pragma unroll
     for (int q = 0; q < PERF; ++q) {
@@ -1012,8 +1022,9 @@ __device__ __forceinline__ void cols_conv_tile(cplx<T>* buf, cplx<T>* __restrict
       for (int r = 0; r < RL; ++r) buf[cidx<T>((g * RL + r) * CW + c)] = u[r];
     }
   }
-  __syncthreads();
-  if constexpr (MID) ct_pass_w<T, N, CW, NT, true, SM, 16>(buf, wm);
+  if constexpr (LOCAL) wave_sync();
+  else __syncthreads();
+  if constexpr (MID) ct_pass_w<T, N, CW, NT, true, SM, 16, false>(buf, wm);
   // last inverse pass (stride N/16, radix 16) straight to HBM: outputs
   // m + S1 r, only r < 8 can be a kept row
 #pragma unroll
