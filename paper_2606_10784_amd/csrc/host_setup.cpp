@@ -13,7 +13,7 @@
 //     the union of its nodes' stencils (no near-field correction: S^alpha).
 #include <algorithm>
 #include <cmath>
-#include <numeric>
+#include <cstdlib>
 
 #include "aim_internal.h"
 
@@ -93,6 +93,55 @@ static inline void lagrange4(double t, double l[4]) {
   l[1] = (t + 1.0) * (t - 1.0) * (t - 2.0) / 2.0;
   l[2] = -(t + 1.0) * t * (t - 2.0) / 2.0;
   l[3] = (t + 1.0) * t * (t - 1.0) / 6.0;
+}
+
+// Near zone: anchor Chebyshev distance <= R (CSR, sorted columns).  Bases are
+// ordered by cell (a stable counting sort by x, then by y); two pointers that
+// run along two cell rows give each basis its near ones in a row as one range.
+// The relation is symmetric: handing out the bases in ascending order fills
+// every row sorted.  Against binary searches and a sort per row, whole tables:
+// 6.5 -> 1.8 ms (3 328 bases, 139 k entries), 43 -> 11 ms (16 384, 1.7 M).
+static void near_zone(HostTables& t) {
+  const int N = t.N, m = t.m, R = t.R, D = 2 * R + 1;
+  std::vector<int32_t> start(m + 1, 0), byx(N), ord(N);
+  for (int j = 0; j < N; ++j) start[t.anc_x[j] + 1]++;
+  for (int x = 0; x < m; ++x) start[x + 1] += start[x];
+  for (int j = 0; j < N; ++j) byx[start[t.anc_x[j]]++] = j;
+  std::fill(start.begin(), start.end(), 0);
+  for (int j = 0; j < N; ++j) start[t.anc_y[j] + 1]++;
+  for (int y = 0; y < m; ++y) start[y + 1] += start[y];
+  {
+    std::vector<int32_t> fill(start.begin(), start.end() - 1);
+    for (int q = 0; q < N; ++q) ord[fill[t.anc_y[byx[q]]]++] = byx[q];
+  }
+  std::vector<int32_t> range((size_t)N * D * 2, 0);   // [basis][dy]: from, to in ord
+  t.nr_ptr.assign(N + 1, 0);
+  for (int y = 0; y < m; ++y) {
+    if (start[y] == start[y + 1]) continue;
+    for (int dy = -R; dy <= R; ++dy) {
+      const int yy = y + dy;
+      if (yy < 0 || yy >= m || start[yy] == start[yy + 1]) continue;
+      int lo = start[yy], hi = lo;
+      const int end = start[yy + 1];
+      for (int q = start[y]; q < start[y + 1]; ++q) {
+        const int i = ord[q], ax = t.anc_x[i];
+        while (lo < end && t.anc_x[ord[lo]] < ax - R) ++lo;
+        while (hi < end && t.anc_x[ord[hi]] <= ax + R) ++hi;
+        int32_t* rg = &range[((size_t)i * D + dy + R) * 2];
+        rg[0] = lo;
+        rg[1] = hi;
+        t.nr_ptr[i + 1] += hi - lo;
+      }
+    }
+  }
+  for (int i = 0; i < N; ++i) t.nr_ptr[i + 1] += t.nr_ptr[i];
+  t.nr_col.resize(t.nr_ptr[N]);
+  std::vector<int32_t> fill(t.nr_ptr.begin(), t.nr_ptr.end() - 1);
+  for (int j = 0; j < N; ++j)
+    for (int d = 0; d < D; ++d) {
+      const int32_t* rg = &range[((size_t)j * D + d) * 2];
+      for (int q = rg[0]; q < rg[1]; ++q) t.nr_col[fill[ord[q]]++] = j;
+    }
 }
 
 aim_status build_host_tables(const aim_params* p, HostTables& t, std::string& err) {
@@ -293,20 +342,34 @@ aim_status build_host_tables(const aim_params* p, HostTables& t, std::string& er
   }
   const int S = t.S;
 
-  // active grid points: union of the map rows, sorted by row-major index
-  std::vector<int64_t> act(lin);
-  std::sort(act.begin(), act.end());
-  act.erase(std::unique(act.begin(), act.end()), act.end());
-  t.n_act = (int)act.size();
-  t.act_ix.resize(t.n_act);
-  t.act_iy.resize(t.n_act);
-  for (int a = 0; a < t.n_act; ++a) {
-    t.act_ix[a] = (int32_t)(act[a] % m);
-    t.act_iy[a] = (int32_t)(act[a] / m);
+  // active grid points: union of the map rows, in row-major order.  One bit
+  // per grid point marks them; a point's number is the count of bits below.
+  {
+    const size_t nw = ((size_t)m * m + 63) / 64;
+    std::vector<uint64_t> bits(nw, 0);
+    std::vector<int32_t> below(nw);
+    for (int64_t l : lin) bits[l >> 6] |= (uint64_t)1 << (l & 63);
+    int32_t na = 0;
+    for (size_t w = 0; w < nw; ++w) {
+      below[w] = na;
+      na += __builtin_popcountll(bits[w]);
+    }
+    t.n_act = na;
+    t.act_ix.resize(na);
+    t.act_iy.resize(na);
+    na = 0;
+    for (size_t w = 0; w < nw; ++w)
+      for (uint64_t b = bits[w]; b; b &= b - 1, ++na) {
+        const int64_t l = (int64_t)w * 64 + __builtin_ctzll(b);
+        t.act_ix[na] = (int32_t)(l % m);
+        t.act_iy[na] = (int32_t)(l / m);
+      }
+    t.aidx.resize((size_t)N * S);
+    for (size_t q = 0; q < lin.size(); ++q) {
+      const int64_t l = lin[q];
+      t.aidx[q] = below[l >> 6] + __builtin_popcountll(bits[l >> 6] & (((uint64_t)1 << (l & 63)) - 1));
+    }
   }
-  t.aidx.resize((size_t)N * S);
-  for (size_t q = 0; q < lin.size(); ++q)
-    t.aidx[q] = (int32_t)(std::lower_bound(act.begin(), act.end(), lin[q]) - act.begin());
   t.y0 = t.act_iy.front();
   t.nr = t.act_iy.back() - t.y0 + 1;
   t.row_ptr.assign(t.nr + 1, 0);
@@ -340,34 +403,7 @@ aim_status build_host_tables(const aim_params* p, HostTables& t, std::string& er
     return AIM_OK;
   }
 
-  // near zone: anchor Chebyshev distance <= R (CSR, sorted columns)
-  std::vector<int64_t> key(N);
-  std::vector<int32_t> ord(N);
-  for (int j = 0; j < N; ++j) key[j] = (int64_t)t.anc_y[j] * m + t.anc_x[j];
-  std::iota(ord.begin(), ord.end(), 0);
-  std::sort(ord.begin(), ord.end(), [&](int a, int b) { return key[a] < key[b] || (key[a] == key[b] && a < b); });
-  std::vector<int64_t> skey(N);
-  for (int q = 0; q < N; ++q) skey[q] = key[ord[q]];
-  const int R = t.R;
-  t.nr_ptr.assign(N + 1, 0);
-  t.nr_col.clear();
-  std::vector<int32_t> cols;
-  for (int i = 0; i < N; ++i) {
-    cols.clear();
-    int ax = t.anc_x[i], ay = t.anc_y[i];
-    for (int dy = -R; dy <= R; ++dy) {
-      int y = ay + dy;
-      if (y < 0 || y >= m) continue;
-      int64_t lo = (int64_t)y * m + std::max(0, ax - R);
-      int64_t hi = (int64_t)y * m + std::min(m - 1, ax + R);
-      auto b = std::lower_bound(skey.begin(), skey.end(), lo);
-      auto e = std::upper_bound(skey.begin(), skey.end(), hi);
-      for (auto it = b; it != e; ++it) cols.push_back(ord[it - skey.begin()]);
-    }
-    std::sort(cols.begin(), cols.end());
-    t.nr_col.insert(t.nr_col.end(), cols.begin(), cols.end());
-    t.nr_ptr[i + 1] = (int32_t)t.nr_col.size();
-  }
+  near_zone(t);
   // Banded symmetric storage of the near field when it pays: bases are
   // numbered along the contour, so near pairs have a small cyclic index
   // distance |i - j|_N <= w, and the near matrices are symmetric (Galerkin,
@@ -377,7 +413,7 @@ aim_status build_host_tables(const aim_params* p, HostTables& t, std::string& er
     int w = 0;
     for (int i = 0; i < N; ++i)
       for (int q = t.nr_ptr[i]; q < t.nr_ptr[i + 1]; ++q) {
-        const int d = ((t.nr_col[q] - i) % N + N) % N;
+        const int d = std::abs(t.nr_col[q] - i);
         w = std::max(w, std::min(d, N - d));
       }
     const double dia_bytes = (double)(w + 1) * N * 16, csr_bytes = (double)t.nr_col.size() * 20;
