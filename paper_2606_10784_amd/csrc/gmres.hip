@@ -437,15 +437,21 @@ __device__ __forceinline__ void rot_apply(double ci, double2 si, double2& a, dou
   a = make_double2(-(si.x * a.x + si.y * a.y) + ci * b.x, -(si.x * a.y - si.y * a.x) + ci * b.y);
 }
 
-// Givens rotations for the Hessenberg columns j0..j1-1 of each rhs: the
-// rotations 0..j0-1 are applied to the new columns in parallel (one thread
-// per column, chains read from LDS), then the new rotations are formed in
-// order.  Writes the residual estimates |g_{j+1}| of those steps.  One block
+// Givens rotations for the Hessenberg columns j0..j1-1 of each rhs, one lane of
+// the first wave per column: the rotations 0..j0-1 are applied to the new
+// columns in parallel (chains read from LDS), then the new rotations are formed
+// in order, each handed to the lanes of the later columns.  g stays in
+// registers.  Writes the residual estimates |g_{j+1}| of those steps.  One block
 // per rhs; dynamic LDS: (j1 - j0) * ldh + 2 * j1 double2.
+// Bound by the serial chain of one wave (12 FP64 operations per earlier rotation)
+// and the square roots and divisions of the new ones.  Batches of eight, against
+// the new rotations formed and applied by one thread with g in memory: 18.0 ->
+// 12.9 us (solve of 128 steps), 23.2 -> 19.3 us (489 steps, restart 400).
 __global__ __launch_bounds__(256) void k_givens_batch(int ldh, int j0, int j1, const int* __restrict__ active,
                                                       double2* H, double2* cs, double2* sn, double2* g,
                                                       double* resid_hist, double* est_out, int est_j0,
                                                       int est_pitch) {
+  static_assert(kCheckEvery + 1 <= 64, "one lane per column");
   extern __shared__ double2 sh[];
   const int r = blockIdx.x;
   if (!active[r]) return;
@@ -454,97 +460,110 @@ __global__ __launch_bounds__(256) void k_givens_batch(int ldh, int j0, int j1, c
   double2* Hs = sh;                        // nc columns of ldh
   double2* Cs = sh + (size_t)nc * ldh;     // j1
   double2* Ss = Cs + j1;                   // j1
-  double2* Hr = H + (size_t)r * ldh * R;
+  double2* Hr = H + ((size_t)r * R + j0) * ldh;
   double2* c = cs + (size_t)r * R;
   double2* s = sn + (size_t)r * R;
-  // the columns j0..j1-1 are contiguous in H (rows 0..j+1 of each are used):
-  // one flat copy with four loads in flight per thread
-  const int tot = nc * ldh;
-  const double2* src = Hr + (size_t)j0 * ldh;
-  for (int b = threadIdx.x; b < tot; b += 4 * 256) {
-    const double2 v0 = src[b], v1 = src[min(b + 256, tot - 1)], v2 = src[min(b + 512, tot - 1)],
-                  v3 = src[min(b + 768, tot - 1)];
-    Hs[b] = v0;
-    if (b + 256 < tot) Hs[b + 256] = v1;
-    if (b + 512 < tot) Hs[b + 512] = v2;
-    if (b + 768 < tot) Hs[b + 768] = v3;
-  }
+  double2* gg = g + (size_t)r * ldh;
+  double2 gj = gg[j0];
   for (int i = threadIdx.x; i < j0; i += 256) {
     Cs[i] = c[i];
     Ss[i] = s[i];
   }
-  __syncthreads();
-  if ((int)threadIdx.x < nc) {
-    double2* col = Hs + (size_t)threadIdx.x * ldh;
-    double2 a = col[0];
-    int i = 0;
-    for (; i + 4 <= j0; i += 4) {   // LDS reads of four rotations ahead of the chain
-      double2 b[4], sq[4];
-      double cq[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        b[q] = col[i + q + 1];
-        cq[q] = Cs[i + q].x;
-        sq[q] = Ss[i + q];
-      }
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        double2 top;
-        rot_apply(cq[q], sq[q], a, b[q], top);
-        col[i + q] = top;
-      }
-    }
-    for (; i < j0; ++i) {
-      double2 top;
-      rot_apply(Cs[i].x, Ss[i], a, col[i + 1], top);
-      col[i] = top;
-    }
-    col[j0] = a;
+  for (int i = threadIdx.x; i <= j1; i += 256) {   // rows 0..j+1 of each column are used
+#pragma unroll 4
+    for (int t = 0; t < nc; ++t) Hs[t * ldh + i] = Hr[t * ldh + i];
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    double2* gg = g + (size_t)r * ldh;
-    for (int t = 0; t < nc; ++t) {
-      const int jj = j0 + t;
-      double2* col = Hs + (size_t)t * ldh;
-      double2 a = col[j0];
-      for (int i = j0; i < jj; ++i) {
+  if (threadIdx.x < 64) {
+    const int t = threadIdx.x;
+    const bool on = t < nc;
+    double2* col = Hs + (size_t)(on ? t : 0) * ldh;
+    double2 a = col[0];
+    int i = 0;
+    if (on && j0 >= 4) {   // LDS reads of four rotations ahead of the chain
+      double2 b[4], sq[4];
+      double cq[4];
+      auto read = [&](int at) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          b[q] = col[at + q + 1];
+          cq[q] = Cs[at + q].x;
+          sq[q] = Ss[at + q];
+        }
+      };
+      read(0);
+      for (; i + 4 <= j0; i += 4) {
+        double2 b0[4], s0[4], top[4];
+        double c0[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          b0[q] = b[q];
+          c0[q] = cq[q];
+          s0[q] = sq[q];
+        }
+        if (i + 8 <= j0) read(i + 4);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) rot_apply(c0[q], s0[q], a, b0[q], top[q]);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) col[i + q] = top[q];
+      }
+    }
+    if (on)
+      for (; i < j0; ++i) {
         double2 top;
         rot_apply(Cs[i].x, Ss[i], a, col[i + 1], top);
         col[i] = top;
       }
+    double2 gtop = make_double2(0, 0), gnext = gtop;   // g_j and g_{j+1} of this lane's step
+    for (int q = 0; q < nc; ++q) {
+      const int jj = j0 + q;
       const double2 b = col[jj + 1];
-      const double na = hypot(a.x, a.y), nb = hypot(b.x, b.y);
-      const double den = hypot(na, nb);
-      double ci;
-      double2 si;
-      if (na == 0.0) {
-        ci = 0.0;
-        si = make_double2(1.0, 0.0);
-      } else {
-        ci = na / den;
-        const double2 ph = make_double2(a.x / na, a.y / na);
-        si = make_double2((ph.x * b.x + ph.y * b.y) / den, (ph.y * b.x - ph.x * b.y) / den);
+      double ci = 0.0;
+      double2 si = make_double2(0, 0);
+      if (t == q) {
+        const double na = hypot(a.x, a.y), nb = hypot(b.x, b.y);
+        const double den = hypot(na, nb);
+        if (na == 0.0) {
+          ci = 0.0;
+          si = make_double2(1.0, 0.0);
+        } else {
+          ci = na / den;
+          const double2 ph = make_double2(a.x / na, a.y / na);
+          si = make_double2((ph.x * b.x + ph.y * b.y) / den, (ph.y * b.x - ph.x * b.y) / den);
+        }
+        Cs[jj] = make_double2(ci, 0.0);
+        Ss[jj] = si;
+        col[jj] = make_double2(ci * a.x + si.x * b.x - si.y * b.y, ci * a.y + si.x * b.y + si.y * b.x);
+        col[jj + 1] = make_double2(0.0, 0.0);
       }
-      Cs[jj] = make_double2(ci, 0.0);
-      Ss[jj] = si;
-      col[jj] = make_double2(ci * a.x + si.x * b.x - si.y * b.y, ci * a.y + si.x * b.y + si.y * b.x);
-      col[jj + 1] = make_double2(0.0, 0.0);
-      const double2 gj = gg[jj];
-      gg[jj + 1] = make_double2(-(si.x * gj.x + si.y * gj.y), -(si.x * gj.y - si.y * gj.x));
-      gg[jj] = make_double2(ci * gj.x, ci * gj.y);
-      resid_hist[(size_t)r * R + jj] = hypot(gg[jj + 1].x, gg[jj + 1].y);
-      // the estimate also goes straight to the host's pinned buffer
-      est_out[(size_t)r * est_pitch + (jj - est_j0)] = resid_hist[(size_t)r * R + jj];
+      ci = __shfl(ci, q);
+      si = make_double2(__shfl(si.x, q), __shfl(si.y, q));
+      if (on && t > q) {
+        double2 top;
+        rot_apply(ci, si, a, b, top);
+        col[jj] = top;
+      }
+      const double2 gn = make_double2(-(si.x * gj.x + si.y * gj.y), -(si.x * gj.y - si.y * gj.x));
+      if (t == q) {
+        gtop = make_double2(ci * gj.x, ci * gj.y);
+        gnext = gn;
+      }
+      gj = gn;
     }
-    __threadfence_system();
+    if (on) {
+      const int jj = j0 + t;
+      gg[jj] = gtop;
+      if (t == nc - 1) gg[j1] = gnext;
+      const double est = hypot(gnext.x, gnext.y);
+      resid_hist[(size_t)r * R + jj] = est;
+      // the estimate also goes straight to the host's pinned buffer
+      est_out[(size_t)r * est_pitch + (jj - est_j0)] = est;
+      __threadfence_system();
+    }
   }
   __syncthreads();
-  double2* dst = Hr + (size_t)j0 * ldh;
-  for (int b = threadIdx.x; b < tot; b += 256) {
-    const int t = b / ldh, i = b - t * ldh;
-    if (i <= j0 + t + 1) dst[b] = Hs[b];
-  }
+  for (int i = threadIdx.x; i <= j1; i += 256)
+    for (int t = max(0, i - j0 - 1); t < nc; ++t) Hr[t * ldh + i] = Hs[t * ldh + i];   // i <= j0 + t + 1
   for (int i = j0 + threadIdx.x; i < j1; i += 256) {
     c[i] = Cs[i];
     s[i] = Ss[i];
@@ -552,32 +571,54 @@ __global__ __launch_bounds__(256) void k_givens_batch(int ldh, int j0, int j1, c
 }
 
 // y = H^-1 g (upper triangular, jm x jm), column-oriented back substitution,
-// one block per right-hand side; dynamic LDS: ldh double2.
-__global__ __launch_bounds__(256) void k_trisolve(int nrhs, int ldh, const int* jm, const double2* H,
-                                                  const double2* g, double2* y) {
+// one block of at least jm threads per right-hand side, a row each; the columns
+// are read kTriAhead steps before their turn.  Dynamic LDS: 2 ldh double2.
+// Bound by the chain of the steps (a division, an LDS round trip and a barrier
+// each); with the column fetched in its step 85 -> 44 us (128 rows), 185 -> 92 us
+// (two cycles of 400 and 89 on average).
+static constexpr int kTriAhead = 8;
+__global__ __launch_bounds__(1024) void k_trisolve(int nrhs, int ldh, const int* jm, const double2* H,
+                                                   const double2* g, double2* y) {
   extern __shared__ double2 gl[];
-  const int r = blockIdx.x;
+  const int r = blockIdx.x, k = threadIdx.x;
   const int R = ldh - 1;
   const int m = jm[r];
+  double2* dl = gl + ldh;   // diagonal
   const double2* Hr = H + (size_t)r * ldh * R;
   const double2* gr = g + (size_t)r * ldh;
   double2* yr = y + (size_t)r * R;
-  for (int i = threadIdx.x; i < m; i += 256) gl[i] = gr[i];
-  __syncthreads();
-  for (int i = m - 1; i >= 0; --i) {
-    const double2* col = Hr + (size_t)i * ldh;
-    const double2 d = col[i];
-    const double dd = d.x * d.x + d.y * d.y;
-    const double2 gi = gl[i];
-    const double2 yi = make_double2((gi.x * d.x + gi.y * d.y) / dd, (gi.y * d.x - gi.x * d.y) / dd);
-    if (threadIdx.x == 0) yr[i] = yi;
-    for (int k = threadIdx.x; k < i; k += 256) {
-      const double2 h = col[k];
-      gl[k] = make_double2(gl[k].x - (h.x * yi.x - h.y * yi.y), gl[k].y - (h.x * yi.y + h.y * yi.x));
-    }
-    __syncthreads();
+  double2 mine = make_double2(0, 0);
+  if (k < m) {
+    mine = gr[k];
+    gl[k] = mine;
+    dl[k] = Hr[(size_t)k * ldh + k];
   }
-  for (int i = m + threadIdx.x; i < R; i += 256) yr[i] = make_double2(0, 0);
+  double2 h[kTriAhead];
+#pragma unroll
+  for (int u = 0; u < kTriAhead; ++u) {
+    const int i = m - 1 - u;
+    if (k < i) h[u] = Hr[(size_t)i * ldh + k];
+  }
+  __syncthreads();
+  for (int i0 = m - 1; i0 >= 0; i0 -= kTriAhead) {
+#pragma unroll
+    for (int u = 0; u < kTriAhead; ++u) {
+      const int i = i0 - u;
+      if (i < 0) break;
+      const double2 d = dl[i];
+      const double dd = d.x * d.x + d.y * d.y;
+      const double2 gi = gl[i];
+      const double2 yi = make_double2((gi.x * d.x + gi.y * d.y) / dd, (gi.y * d.x - gi.x * d.y) / dd);
+      if (k == i) yr[i] = yi;
+      if (k < i) {
+        mine = make_double2(mine.x - (h[u].x * yi.x - h[u].y * yi.y), mine.y - (h[u].x * yi.y + h[u].y * yi.x));
+        if (k == i - 1) gl[k] = mine;
+        if (k < i - kTriAhead) h[u] = Hr[(size_t)(i - kTriAhead) * ldh + k];
+      }
+      __syncthreads();
+    }
+  }
+  for (int i = m + threadIdx.x; i < R; i += blockDim.x) yr[i] = make_double2(0, 0);
 }
 
 __global__ void k_set_g0(int nrhs, int ldh, const double2* nrm2, const int* active, double2* g) {
@@ -973,9 +1014,10 @@ struct GmresRun {
     int* d_jm = (int*)w.part;   // scratch: jm then mask
     AIM_HIP_CHECK(put_mask(d_jm, jdone));
     AIM_HIP_CHECK(put_mask(w.active, upd));
-    hipLaunchKernelGGL(k_trisolve, dim3(nrhs), dim3(256), (size_t)ldh * 16, s, nrhs, ldh, d_jm, w.H, w.g, w.y);
     int jmax = 0;
     for (int r = 0; r < nrhs; ++r) jmax = std::max(jmax, jdone[r]);
+    hipLaunchKernelGGL(k_trisolve, dim3(nrhs), dim3(std::max(jmax + 255, 256) / 256 * 256), 2 * (size_t)ldh * 16, s,
+                       nrhs, ldh, d_jm, w.H, w.g, w.y);
     if (jmax > 0)
       hipLaunchKernelGGL(k_gemv, dim3((N + GV_ROWS - 1) / GV_ROWS, nrhs), dim3(256), 0, s, N, jmax, w.V, ldv, w.y,
                          (int64_t)restart, 1.0, w.active, x, (int64_t)N);
