@@ -249,6 +249,14 @@ struct ProfScope {
   }
 };
 
+// The transposed map rows (grid point -> contributing bases) of up to three
+// channels, in the precision of the grid.
+struct AtMap {
+  const int32_t* ptr = nullptr;
+  const int32_t* basis = nullptr;
+  const void* w[3] = {nullptr, nullptr, nullptr};
+};
+
 // kernels / launchers (aim_kernels.hip)
 aim_status dev_alloc(Ctx* c, void** p, size_t bytes);
 aim_status setup_device(Ctx* c);                        // tables, spectrum, near field

@@ -573,32 +573,14 @@ template <int CB, int N> constexpr int tiles_kept(int kcut) {
 
 template <int N> constexpr int row_threads() { return N / 16 < 64 ? 64 : (N / 16 > 256 ? 256 : N / 16); }
 
-// Pass 1: gather active values of a row into a zeroed LDS row, FFT along x.
-// Active points have x < N/2, so only that half is cleared and the first pass
-// reads inputs 0..7 of its radix-16 butterflies.
-template <typename T, int N, bool CUT>
-__global__ __launch_bounds__(row_threads<N>()) void k_rows_fwd(
-    const cplx<T>* __restrict__ U, int n_act, const int32_t* __restrict__ row_ptr,
-    const int32_t* __restrict__ act_ix, int nr, int ldt, int keep, cplx<T>* __restrict__ Tb,
-    const cplx<T>* __restrict__ tw) {
+// The row FFT of pass 1 on a row in LDS (inputs x < N/2), stored to the tiles.
+template <typename T, int N, int NT, bool CUT, int NWT>
+__device__ __forceinline__ void row_fft_store(cplx<T>* buf, cplx<T> (&wt)[NWT], int row, int pair, int ldt, int keep,
+                                              cplx<T>* __restrict__ Tb) {
   using V = cplx<T>;
-  static_assert(N >= 32, "row pass assumes at least two forward passes");
-  constexpr int NT = row_threads<N>();
   constexpr int CB = ColCfg<T, N>::CB;
   constexpr int NBLK = N / CB;
-  __shared__ V buf[padded(N)];
-  const int row = xcd_row(blockIdx.x, nr), pair = blockIdx.y;
   const int tid = threadIdx.x;
-  if (row >= nr) return;
-  constexpr int NW = chain_len<N, NT, 16, N, false>();
-  V wt[NW > 0 ? NW : 1];
-  chain_tw<T, N, NT, 16, N, false>(tw, wt);
-  for (int i = tid; i < N / 2; i += NT) buf[pidx(i)] = mk<T>(0, 0);
-  __syncthreads();
-  const int a0 = row_ptr[row], a1 = row_ptr[row + 1];
-  const V* Up = U + (size_t)pair * n_act;
-  for (int a = a0 + tid; a < a1; a += NT) buf[pidx(act_ix[a])] = Up[a];
-  __syncthreads();
   {
     constexpr int NB = N / 16, PER = (NB + NT - 1) / NT;
     V v[PER][16];
@@ -643,6 +625,112 @@ __global__ __launch_bounds__(row_threads<N>()) void k_rows_fwd(
     if (((N % NT) == 0 || idx < N) && (!CUT || tile_kept<NBLK>(idx / CB, keep)))
       out[(size_t)(idx / CB) * ldt * CB + idx % CB] = v[q];
   }
+}
+
+// Pass 1: gather active values of a row into a zeroed LDS row, FFT along x.
+// Active points have x < N/2, so only that half is cleared and the first pass
+// reads inputs 0..7 of its radix-16 butterflies.
+template <typename T, int N, bool CUT>
+__global__ __launch_bounds__(row_threads<N>()) void k_rows_fwd(
+    const cplx<T>* __restrict__ U, int n_act, const int32_t* __restrict__ row_ptr,
+    const int32_t* __restrict__ act_ix, int nr, int ldt, int keep, cplx<T>* __restrict__ Tb,
+    const cplx<T>* __restrict__ tw) {
+  using V = cplx<T>;
+  static_assert(N >= 32, "row pass assumes at least two forward passes");
+  constexpr int NT = row_threads<N>();
+  __shared__ V buf[padded(N)];
+  const int row = xcd_row(blockIdx.x, nr), pair = blockIdx.y;
+  const int tid = threadIdx.x;
+  if (row >= nr) return;
+  constexpr int NW = chain_len<N, NT, 16, N, false>();
+  V wt[NW > 0 ? NW : 1];
+  chain_tw<T, N, NT, 16, N, false>(tw, wt);
+  for (int i = tid; i < N / 2; i += NT) buf[pidx(i)] = mk<T>(0, 0);
+  __syncthreads();
+  const int a0 = row_ptr[row], a1 = row_ptr[row + 1];
+  const V* Up = U + (size_t)pair * n_act;
+  for (int a = a0 + tid; a < a1; a += NT) buf[pidx(act_ix[a])] = Up[a];
+  __syncthreads();
+  row_fft_store<T, N, NT, CUT>(buf, wt, row, pair, ldt, keep, Tb);
+}
+
+// Pass 1 with the anterpolation in it, for launches of few rows: the U values of
+// a row are summed where they are used, 16 lanes per point (lane sums and their
+// order as in the anterpolation kernel), four points per lane group in flight.
+// Saves a launch and a trip through memory; bound by the chain of dependent
+// loads (row, point, entry, value).  The FFT leaves most of the block's threads
+// idle, so launches of many rows are better off with the separate kernels.
+static constexpr int kAtThreads = 256;
+template <typename T, typename TW, int N, bool CUT>
+__global__ __launch_bounds__(kAtThreads) void k_rows_fwd_at(AtMap at, const double2* __restrict__ x, int64_t ldx,
+                                                            int nrhs, const int32_t* __restrict__ row_ptr,
+                                                            const int32_t* __restrict__ act_ix, int nr, int ldt,
+                                                            int keep, cplx<T>* __restrict__ Tb,
+                                                            const cplx<T>* __restrict__ tw) {
+  using V = cplx<T>;
+  constexpr int NT = kAtThreads, NG = NT / 16, GU = 4;
+  __shared__ V buf[padded(N)];
+  const int row = xcd_row(blockIdx.x, nr), pair = blockIdx.y, ch = pair / nrhs;
+  const int tid = threadIdx.x, l = tid & 15;
+  if (row >= nr) return;
+  const int a0 = row_ptr[row], a1 = row_ptr[row + 1];
+  constexpr int NW = chain_len<N, NT, 16, N, false>();
+  V wt[NW > 0 ? NW : 1];
+  chain_tw<T, N, NT, 16, N, false>(tw, wt);
+  for (int i = tid; i < N / 2; i += NT) buf[pidx(i)] = mk<T>(0, 0);
+  __syncthreads();
+  const TW* w = (const TW*)(ch == 0 ? at.w[0] : (ch == 1 ? at.w[1] : at.w[2]));
+  const double2* xr = x + (size_t)(pair - ch * nrhs) * ldx;
+  for (int a = a0 + (tid >> 4); a < a1; a += NG * GU) {
+    int e[GU], e1[GU], ix[GU];
+    T sx[GU], sy[GU];
+#pragma unroll
+    for (int u = 0; u < GU; ++u) {
+      const int p = a + u * NG;
+      const bool on = p < a1;
+      e[u] = on ? at.ptr[p] + l : 0;
+      e1[u] = on ? at.ptr[p + 1] : 0;
+      ix[u] = on ? act_ix[p] : -1;
+      sx[u] = sy[u] = 0;
+    }
+    bool more;
+    do {
+      int b[GU][2];
+      T we[GU][2];
+      more = false;
+#pragma unroll
+      for (int u = 0; u < GU; ++u)
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          if (e[u] + 16 * h < e1[u]) {
+            b[u][h] = at.basis[e[u] + 16 * h];
+            we[u][h] = (T)w[e[u] + 16 * h];
+          }
+#pragma unroll
+      for (int u = 0; u < GU; ++u) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          if (e[u] + 16 * h < e1[u]) {
+            const double2 xv = xr[b[u][h]];
+            sx[u] += we[u][h] * (T)xv.x;
+            sy[u] += we[u][h] * (T)xv.y;
+          }
+        e[u] += 32;
+        more |= e[u] < e1[u];
+      }
+    } while (more);
+#pragma unroll
+    for (int u = 0; u < GU; ++u) {
+#pragma unroll
+      for (int off = 8; off >= 1; off >>= 1) {
+        sx[u] += __shfl_xor(sx[u], off, 16);
+        sy[u] += __shfl_xor(sy[u], off, 16);
+      }
+      if (l == 0 && ix[u] >= 0) buf[pidx(ix[u])] = mk<T>(sx[u], sy[u]);
+    }
+  }
+  __syncthreads();
+  row_fft_store<T, N, NT, CUT>(buf, wt, row, pair, ldt, keep, Tb);
 }
 
 // Pass 3: inverse FFT along x, gather the active points of the row.  The
@@ -1122,6 +1210,19 @@ bool rows_few(int kcut, int n_act, int nr, int& pk) {
   pk = tiles_kept<ColCfg<T, N>::CB, N>(kcut) * (ColCfg<T, N>::CB / 2);
   return N >= 512 && pk <= N / 16 && 5 * (int64_t)pk * n_act <= 3 * (int64_t)N * nr;
 }
+template <typename T> bool rows_few_n(int n, int kcut, int n_act, int nr) {
+  int pk;
+  switch (n) {
+#define CASE(NN) \
+  case NN: return rows_few<T, NN>(kcut, n_act, nr, pk);
+    AIM_FOR_SIZES(CASE)
+#undef CASE
+  }
+  return false;
+}
+bool rows_few_columns(int n, bool f32, int kcut, int n_act, int nr) {
+  return f32 ? rows_few_n<float>(n, kcut, n_act, nr) : rows_few_n<double>(n, kcut, n_act, nr);
+}
 template <typename T, int N>
 void rows_fwd(const cplx<T>* U, int n_act, const int32_t* row_ptr, const int32_t* act_ix, int nr, int ldt, int kcut,
               int pairs, cplx<T>* Tb, const cplx<T>* tw, hipStream_t s) {
@@ -1174,6 +1275,43 @@ aim_status launch_rows_fwd(int n, const cplx<T>* U, int n_act, const int32_t* ro
 #define CASE(NN) \
   case NN: rows_fwd<T, NN>(U, n_act, row_ptr, act_ix, nr, ldt, kcut, pairs, Tb, tw, s); break;
     AIM_FOR_SIZES(CASE)
+#undef CASE
+    default: return AIM_E_ARG;
+  }
+  return hipGetLastError() == hipSuccess ? AIM_OK : AIM_E_HIP;
+}
+
+// Whether pass 1 takes the anterpolation along: the whole launch is on the chip
+// at once.  Whole products, separate / fused in us, by rows times pairs:
+//   FP64  n = 128:  56  20.5 / 18.7   448  25.2 / 24.1   1344  40.8 / 41.5
+//         n = 512: 214  22.0 / 21.0   856  31.2 / 31.0   1712  47.4 / 48.0
+//   FP32  n = 512: 214  21.8 / 20.8  1284  30.3 / 29.3   2568  45.3 / 45.9
+// From n = 1024 on a block of 256 threads is compiled to other fused multiply-
+// adds than the separate kernel (a column would depend on its batch), and one
+// of as many threads as that kernel's is slower (28.7 / 33.4).
+bool rows_fwd_at_fits(int n, bool f32, int nr, int pairs) {
+  return n <= 512 && (int64_t)nr * pairs <= (f32 ? 1536 : 768);
+}
+
+template <typename T, typename TW>
+aim_status launch_rows_fwd_at(int n, const AtMap& at, const double2* x, int64_t ldx, int nrhs, const int32_t* row_ptr,
+                              const int32_t* act_ix, int nr, int ldt, int kcut, int pairs, cplx<T>* Tb,
+                              const cplx<T>* tw, hipStream_t s) {
+  if (ldt < nr) return AIM_E_ARG;
+  const dim3 g(8 * ((nr + 7) / 8), pairs), b(kAtThreads);
+  switch (n) {
+#define CASE(NN)                                                                                                      \
+  case NN: {                                                                                                          \
+    const int keep = tiles_kept<ColCfg<T, NN>::CB, NN>(kcut);                                                         \
+    if (keep == NN / ColCfg<T, NN>::CB - 1)                                                                           \
+      hipLaunchKernelGGL((k_rows_fwd_at<T, TW, NN, false>), g, b, 0, s, at, x, ldx, nrhs, row_ptr, act_ix, nr, ldt,   \
+                         keep, Tb, tw);                                                                               \
+    else                                                                                                              \
+      hipLaunchKernelGGL((k_rows_fwd_at<T, TW, NN, true>), g, b, 0, s, at, x, ldx, nrhs, row_ptr, act_ix, nr, ldt,    \
+                         keep, Tb, tw);                                                                               \
+    break;                                                                                                            \
+  }
+    CASE(32) CASE(64) CASE(128) CASE(256) CASE(512)
 #undef CASE
     default: return AIM_E_ARG;
   }
@@ -1275,6 +1413,12 @@ template aim_status launch_rows_fwd<double>(int, const double2*, int, const int3
                                             double2*, const double2*, hipStream_t);
 template aim_status launch_rows_fwd<float>(int, const float2*, int, const int32_t*, const int32_t*, int, int, int, int,
                                            float2*, const float2*, hipStream_t);
+template aim_status launch_rows_fwd_at<double, double>(int, const AtMap&, const double2*, int64_t, int, const int32_t*,
+                                                      const int32_t*, int, int, int, int, double2*, const double2*,
+                                                      hipStream_t);
+template aim_status launch_rows_fwd_at<float, float>(int, const AtMap&, const double2*, int64_t, int, const int32_t*,
+                                                    const int32_t*, int, int, int, int, float2*, const float2*,
+                                                    hipStream_t);
 template aim_status launch_rows_inv<double>(int, const double2*, int, int, int, const int32_t*, const int32_t*, int,
                                             double2*, int, const double2*, hipStream_t);
 template aim_status launch_rows_inv<float>(int, const float2*, int, int, int, const int32_t*, const int32_t*, int,
