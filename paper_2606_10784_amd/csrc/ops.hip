@@ -717,7 +717,7 @@ __global__ __launch_bounds__(256) void k_anterp(int n_act, int nrhs, const int32
 // ---------------------------------------------------------------------------
 template <typename T, typename TW, int LANES>
 __global__ __launch_bounds__(256) void k_interp_near(
-    int N, int nrhs, int nch, int S, const TW* __restrict__ W0, const TW* __restrict__ W1,
+    int N, int nrhs, int rpb, int nch, int S, const TW* __restrict__ W0, const TW* __restrict__ W1,
     const TW* __restrict__ W2, double sg, const int32_t* __restrict__ aidx,
     const cplx<T>* __restrict__ V, int n_act, const int32_t* __restrict__ nptr,
     const int32_t* __restrict__ ncol, const double2* __restrict__ C, const double2* __restrict__ x,
@@ -732,7 +732,8 @@ __global__ __launch_bounds__(256) void k_interp_near(
   const double w1 = (st && nch > 1) ? (double)W1[o] : 0.0;
   const double w2 = (st && nch > 1) ? (double)W2[o] : 0.0;
   const int q0 = C ? nptr[row] : 0, q1 = C ? nptr[row + 1] : 0;
-  for (int r = 0; r < nrhs; ++r) {
+  const int r0 = blockIdx.y * rpb, r1 = min(nrhs, r0 + rpb);   // this block's right-hand sides
+  for (int r = r0; r < r1; ++r) {
     double ax = 0.0, ay = 0.0;
     if (st) {
       const cplx<T> v0 = V[(size_t)r * n_act + a];
@@ -800,13 +801,28 @@ __global__ void k_near_to_band(int64_t nnz, int N, int w, const int32_t* __restr
 
 // band widths below this take the several-rhs form of the band product
 constexpr int kBandFastW = 64;
+// A batch's right-hand sides are split over blocks while the launch has fewer
+// than this many (six per CU): a block takes its share one after the other.
+// Whole products, unsplit / split in us: 24 right-hand sides, N = 1024 (64
+// blocks) 58.7 / 42.7, N = 3000 110 / 65, N = 6000 153 / 118; 8 right-hand
+// sides, N = 1024 31.3 / 26.1.  From a thousand blocks on the shared band
+// values are worth more (N = 16 000, two right-hand sides 85.0 / 86.9).
+constexpr int kInterpBlocks = 1536;
+struct RhsSplit {
+  int per, blocks;   // right-hand sides per block, blocks along y
+  RhsSplit(int nrhs, unsigned gx) {
+    const int ny = std::max(1, std::min(nrhs, kInterpBlocks / (int)gx));
+    per = (nrhs + ny - 1) / ny;
+    blocks = (nrhs + per - 1) / per;
+  }
+};
 
 // interpolation + banded near field, 16 lanes per basis row:
 //   y_i = scale * ( sum_ch sgn_ch W_ch . V_ch + sum_{d<=w} Cd[d][i] x_{i+d}
 //                   + sum_{1<=d<=w} Cd[d][i-d] x_{i-d} )   (indices mod N)
 template <typename T, typename TW, bool FAST>
 __global__ __launch_bounds__(256) void k_interp_band(
-    int N, int nrhs, int nch, const TW* __restrict__ W0, const TW* __restrict__ W1, const TW* __restrict__ W2,
+    int N, int nrhs, int rpb, int nch, const TW* __restrict__ W0, const TW* __restrict__ W1, const TW* __restrict__ W2,
     double sg, const int32_t* __restrict__ aidx, const cplx<T>* __restrict__ V, int n_act, int w,
     const double2* __restrict__ Cd, const double2* __restrict__ x, int64_t ldx, double2* __restrict__ y,
     int64_t ldy, double2 scale) {
@@ -831,7 +847,8 @@ __global__ __launch_bounds__(256) void k_interp_band(
   // (the same for every rhs) are loaded once, ahead of everything else, and
   // each rhs issues all its x loads before its first sum; the terms are
   // added in the order of the general loop below.  The held values take
-  // registers (a third of the occupancy), which one rhs does not repay.
+  // registers (a third of the occupancy), which one rhs of a long contour
+  // does not repay.
   constexpr int KU = kBandFastW / L;
   double2 cu[KU], cl[KU];
   int ju[KU], il[KU];
@@ -845,7 +862,8 @@ __global__ __launch_bounds__(256) void k_interp_band(
       cl[k] = dl <= w ? Cd[(size_t)dl * N + il[k]] : make_double2(0.0, 0.0);
     }
   }
-  for (int r = 0; r < nrhs; ++r) {
+  const int r0 = blockIdx.y * rpb, r1 = min(nrhs, r0 + rpb);   // this block's right-hand sides
+  for (int r = r0; r < r1; ++r) {
     const double2* xr = x + (size_t)r * ldx;
     double2 xu[KU], xl[KU];
     if constexpr (FAST) {
@@ -1631,14 +1649,16 @@ static void launch_interp(Ctx* c, const int* chans, int nch, double sg, const do
                           const double2* x, int64_t ldx, double2* y, int64_t ldy, double2 scale) {
   HostTables& t = c->t;
   const int threads = 256;
-  dim3 g((unsigned)(((size_t)t.N * LANES + threads - 1) / threads));
+  const unsigned gx = (unsigned)(((size_t)t.N * LANES + threads - 1) / threads);
+  const RhsSplit rs(nrhs, gx);
+  const dim3 g(gx, rs.blocks);
   const cplx<T>* V = (const cplx<T>*)c->d_V;
   if (sizeof(T) == 4) {
-    hipLaunchKernelGGL((k_interp_near<T, float, LANES>), g, dim3(threads), 0, c->stream, t.N, nrhs, nch, t.S,
+    hipLaunchKernelGGL((k_interp_near<T, float, LANES>), g, dim3(threads), 0, c->stream, t.N, nrhs, rs.per, nch, t.S,
                        c->d_Wf[chans[0]], c->d_Wf[chans[nch > 1 ? 1 : 0]], c->d_Wf[chans[nch > 2 ? 2 : 0]], sg,
                        c->d_aidx, V, t.n_act, c->d_nr_ptr, c->d_nr_col, C, x, ldx, y, ldy, scale);
   } else {
-    hipLaunchKernelGGL((k_interp_near<T, double, LANES>), g, dim3(threads), 0, c->stream, t.N, nrhs, nch, t.S,
+    hipLaunchKernelGGL((k_interp_near<T, double, LANES>), g, dim3(threads), 0, c->stream, t.N, nrhs, rs.per, nch, t.S,
                        c->d_W[chans[0]], c->d_W[chans[nch > 1 ? 1 : 0]], c->d_W[chans[nch > 2 ? 2 : 0]], sg,
                        c->d_aidx, V, t.n_act, c->d_nr_ptr, c->d_nr_col, C, x, ldx, y, ldy, scale);
   }
@@ -1655,10 +1675,14 @@ static aim_status interp(Ctx* c, const int* chans, int nch, double sg, bool near
     const double2* Cd = !near ? nullptr : (Cn == c->d_CS ? c->d_CSd : c->d_CNd);
     // a multiple of 8 blocks (the kernel's XCD-aware order); the extra ones exit
     const size_t nb = ((size_t)t.N * 16 + 255) / 256;
-    dim3 g((unsigned)(8 * ((nb + 7) / 8)));
-    const bool fast = Cd && nrhs > 1 && t.band_w < kBandFastW;
+    const unsigned gx = (unsigned)(8 * ((nb + 7) / 8));
+    const RhsSplit rs(nrhs, gx);
+    const dim3 g(gx, rs.blocks);
+    // one right-hand side repays the held band values while the launch is on
+    // the chip at once (N = 512 20.5 -> 19.9 us, N = 16 384 55.5 -> 54.7 us)
+    const bool fast = Cd && t.band_w < kBandFastW && (nrhs > 1 || gx <= 1024);
 #define AIM_BAND(TW, WT, F)                                                                                   \
-  hipLaunchKernelGGL((k_interp_band<T, TW, F>), g, dim3(256), 0, c->stream, t.N, nrhs, nch, WT[chans[0]],     \
+  hipLaunchKernelGGL((k_interp_band<T, TW, F>), g, dim3(256), 0, c->stream, t.N, nrhs, rs.per, nch, WT[chans[0]], \
                      WT[chans[nch > 1 ? 1 : 0]], WT[chans[nch > 2 ? 2 : 0]], sg, c->d_aidx, (const cplx<T>*)c->d_V, \
                      t.n_act, t.band_w, Cd, x, ldx, y, ldy, scale)
     if (sizeof(T) == 4) {
