@@ -516,9 +516,9 @@ template <typename T, int N> struct ColCfg {
 // same XCD, so the parts of each tile line meet in one L2.
 // Tiles past the first `keep` but the last are left out: block positions keep
 // .. hold the last tile, then nothing (false).
-template <typename T, int N>
+template <typename T, int N, int CW>
 __device__ __forceinline__ bool col_block_of(int b, int keep, int& tb, int& c0) {
-  constexpr int CB = ColCfg<T, N>::CB, CW = ColCfg<T, N>::CW, K = CB / CW;   // blocks per tile
+  constexpr int CB = ColCfg<T, N>::CB, K = CB / CW;   // blocks per tile
   if constexpr (K == 1) {
     tb = b;
     c0 = 0;
@@ -531,8 +531,8 @@ __device__ __forceinline__ bool col_block_of(int b, int keep, int& tb, int& c0) 
   if (tb == keep) tb = N / CB - 1;
   return true;
 }
-template <typename T, int N> int col_blocks(int keep) {
-  constexpr int K = ColCfg<T, N>::CB / ColCfg<T, N>::CW;
+template <typename T, int N, int CW> int col_blocks(int keep) {
+  constexpr int K = ColCfg<T, N>::CB / CW;
   return K == 1 ? keep + 1 : (keep + 8) / 8 * 8 * K;
 }
 
@@ -971,14 +971,13 @@ __global__ __launch_bounds__(row_threads<N>()) void k_rows_fft_inplace(cplx<T>* 
 // The column pass of CW columns of one tile [row][CB] (nr kept rows, the rest of the
 // column is the zero padding), in place: column FFT, spectrum multiply,
 // inverse column FFT (the MODE 0 body of k_cols and of k_cols_group).
-template <typename T, int N>
+template <typename T, int N, int CW, int NT>
 __device__ __forceinline__ void cols_conv_tile(cplx<T>* buf, cplx<T>* __restrict__ tile, int nr, int b, int c0_,
                                                const cplx<T>* __restrict__ Cq, const cplx<T>* __restrict__ tw) {
   using V = cplx<T>;
   constexpr int CB = ColCfg<T, N>::CB;   // tile width (global layout)
-  constexpr int CW = ColCfg<T, N>::CW;   // columns of this block, c0 .. c0 + CW - 1 (LDS layout)
+  // CW: columns of this block, c0 .. c0 + CW - 1 (LDS layout); NT: its threads
   const int c0 = CW == CB ? 0 : c0_;
-  constexpr int NT = ColCfg<T, N>::NT;
   const int tid = threadIdx.x;
   static_assert(N >= 32, "column pass assumes at least two forward passes");
   constexpr int RL = last_radix<N>();
@@ -990,7 +989,7 @@ __device__ __forceinline__ void cols_conv_tile(cplx<T>* buf, cplx<T>* __restrict
   constexpr int NBM = (N / 16) * CW, PERM = (NBM + NT - 1) / NT;
   constexpr int NG = N / RL, NBF = NG * CW, PERF = (NBF + NT - 1) / NT;
   // the last passes' groups of a wave are the positions of its middle passes
-  constexpr bool LOCAL = MID && NT == 256 && NB1 == 256 && NBF == 256 * PERF;
+  constexpr bool LOCAL = MID && (NT == 256 || NT == 64) && NB1 == NT && NBF == NT * PERF;
   // forward pass 1 (stride N/16, radix 16) from HBM: inputs m + S1 r with
   // r >= 8 lie in the zero half
   V v[PER1][16];
@@ -1149,8 +1148,8 @@ __global__ __launch_bounds__((ColCfg<T, N>::NT)) void k_cols(
   const int tid = threadIdx.x;
   if constexpr (MODE == 0) {
     int tb, c0;
-    if (!col_block_of<T, N>(b, keep, tb, c0)) return;
-    cols_conv_tile<T, N>(buf, Tb + ((size_t)pair * NBLK + tb) * ldt * CB, nr, tb, c0, Cq, tw);
+    if (!col_block_of<T, N, CW>(b, keep, tb, c0)) return;
+    cols_conv_tile<T, N, CW, NT>(buf, Tb + ((size_t)pair * NBLK + tb) * ldt * CB, nr, tb, c0, Cq, tw);
   } else {
     const int kx0 = b * CW;
     for (int idx = tid; idx < N * CW; idx += NT) {
@@ -1166,6 +1165,23 @@ __global__ __launch_bounds__((ColCfg<T, N>::NT)) void k_cols(
   }
 }
 
+// Blocks of one wave, with as many columns as give each lane one radix-16
+// butterfly: the same transforms on more CUs, no barriers between waves, less
+// LDS traffic per CU.  For n = 256 always: column pass of seven right-hand sides
+// 8.6 -> 6.0 us, whole products 19.5 -> 17.8 us (one) and 44.1 -> 39.8 us (24).
+// For n = 512 while the wide blocks leave CUs idle (cols_narrow).  For n = 128
+// the compiler picks other fused multiply-adds.
+template <int N> constexpr int narrow_cols() { return N == 256 ? 4 : (N == 512 ? 2 : 0); }
+template <typename T, int N>
+__global__ __launch_bounds__(64) void k_cols_narrow(cplx<T>* __restrict__ Tb, int nr, int ldt, int keep,
+                                                    const cplx<T>* __restrict__ Cq, const cplx<T>* __restrict__ tw) {
+  constexpr int CB = ColCfg<T, N>::CB, CW = narrow_cols<N>();
+  __shared__ cplx<T> buf[padded(N * CW)];
+  int tb, c0;
+  if (!col_block_of<T, N, CW>(blockIdx.x, keep, tb, c0)) return;
+  cols_conv_tile<T, N, CW, 64>(buf, Tb + ((size_t)blockIdx.y * (N / CB) + tb) * ldt * CB, nr, tb, c0, Cq, tw);
+}
+
 // Column passes of several contexts that share one spectrum (same n, k eps
 // and precision), one launch: entry e of the batch is a pair's tile set
 // (tile base of column block 0, kept rows, tile stride); blockIdx.y picks
@@ -1177,18 +1193,18 @@ struct ColBatch {
   int ldt[kMax];
 };
 
-template <typename T, int N>
-__global__ __launch_bounds__((ColCfg<T, N>::NT)) void k_cols_group(ColBatch batch, int keep,
+template <typename T, int N, int CW, int NT>
+__global__ __launch_bounds__(NT) void k_cols_group(ColBatch batch, int keep,
                                                                  const cplx<T>* __restrict__ Cq,
                                                                  const cplx<T>* __restrict__ tw) {
   using V = cplx<T>;
   constexpr int CB = ColCfg<T, N>::CB;
-  __shared__ V buf[padded(N * ColCfg<T, N>::CW)];
+  __shared__ V buf[padded(N * CW)];
   const int e = blockIdx.y;
   int tb, c0;
-  if (!col_block_of<T, N>(blockIdx.x, keep, tb, c0)) return;
+  if (!col_block_of<T, N, CW>(blockIdx.x, keep, tb, c0)) return;
   V* tile = (V*)batch.tile[e] + (size_t)tb * batch.ldt[e] * CB;
-  cols_conv_tile<T, N>(buf, tile, batch.nr[e], tb, c0, Cq, tw);
+  cols_conv_tile<T, N, CW, NT>(buf, tile, batch.nr[e], tb, c0, Cq, tw);
 }
 
 // ---------------------------------------------------------------------------
@@ -1333,22 +1349,42 @@ aim_status launch_rows_inv(int n, const cplx<T>* Tb, int nr, int ldt, int kcut, 
   return hipGetLastError() == hipSuccess ? AIM_OK : AIM_E_HIP;
 }
 
+// n = 512, whole products, wide / narrow blocks in us, by pairs (64 tiles each in
+// FP64, 32 in FP32): FP64 1 20.8 / 20.0, 2 22.9 / 22.4, 3 26.0 / 26.3, 4 30.3 / 31.1;
+// FP32 1 20.6 / 18.7, 4 23.9 / 23.0, 6 26.9 / 26.6, 8 31.8 / 32.1.
+template <typename T, int N> bool cols_narrow(int keep, int pairs) {
+  return N == 256 || (N == 512 && (int64_t)(keep + 1) * pairs <= (sizeof(T) == 8 ? 128 : 192));
+}
+template <typename T, int N>
+void cols_conv(cplx<T>* Tb, int nr, int ldt, int kcut, int pairs, const cplx<T>* Cq, const cplx<T>* tw, hipStream_t s,
+               hipEvent_t ev_start, hipEvent_t ev_stop) {
+  constexpr int CW = ColCfg<T, N>::CW, NW = narrow_cols<N>();
+  const int keep = tiles_kept<ColCfg<T, N>::CB, N>(kcut);
+  if constexpr (NW > 0)
+    if (cols_narrow<T, N>(keep, pairs)) {
+      hipExtLaunchKernelGGL((k_cols_narrow<T, N>), dim3(col_blocks<T, N, NW>(keep), pairs), dim3(64), 0, s, ev_start,
+                            ev_stop, 0, Tb, nr, ldt, keep, Cq, tw);
+      return;
+    }
+  if constexpr (N != 256)
+    hipExtLaunchKernelGGL((k_cols<T, N, 0>), dim3(col_blocks<T, N, CW>(keep), pairs), dim3(ColCfg<T, N>::NT), 0, s,
+                          ev_start, ev_stop, 0, Tb, nr, ldt, keep, Cq, tw);
+}
+
 template <typename T>
 aim_status launch_cols(int n, int mode, cplx<T>* Tb, int nr, int ldt, int kcut, int pairs, const cplx<T>* Cq,
                        const cplx<T>* tw, hipStream_t s, hipEvent_t ev_start, hipEvent_t ev_stop) {
   // kept rows lie in the unpadded half
   if (mode == 0 && (nr < 1 || nr > n / 2 || ldt < nr)) return AIM_E_ARG;
   switch (n) {
-#define CASE(NN)                                                                                                     \
-  case NN: {                                                                                                         \
-    const int keep = tiles_kept<ColCfg<T, NN>::CB, NN>(kcut);                                                        \
-    const dim3 g(col_blocks<T, NN>(keep), pairs), b(ColCfg<T, NN>::NT);                                              \
-    if (mode != 0)                                                                                                   \
-      hipLaunchKernelGGL((k_cols<T, NN, 1>), dim3(NN / ColCfg<T, NN>::CW, pairs), b, 0, s, Tb, nr, ldt, 0, Cq, tw);  \
-    else                                                                                                             \
-      hipExtLaunchKernelGGL((k_cols<T, NN, 0>), g, b, 0, s, ev_start, ev_stop, 0, Tb, nr, ldt, keep, Cq, tw);        \
-    break;                                                                                                           \
-  }
+#define CASE(NN)                                                                                                  \
+  case NN:                                                                                                        \
+    if (mode != 0)                                                                                                \
+      hipLaunchKernelGGL((k_cols<T, NN, 1>), dim3(NN / ColCfg<T, NN>::CW, pairs), dim3(ColCfg<T, NN>::NT), 0, s,  \
+                         Tb, nr, ldt, 0, Cq, tw);                                                                 \
+    else                                                                                                          \
+      cols_conv<T, NN>(Tb, nr, ldt, kcut, pairs, Cq, tw, s, ev_start, ev_stop);                                   \
+    break;
     AIM_FOR_SIZES(CASE)
 #undef CASE
     default: return AIM_E_ARG;
@@ -1381,14 +1417,14 @@ aim_status launch_cols_group(int n, int count, void* const* tiles, const int* nr
     bt.ldt[e] = ldt[q];
   }
   switch (n) {
-#define CASE(NN)                                                                                              \
-  case NN:                                                                                                    \
-    {                                                                                                         \
-      const int keep = tiles_kept<ColCfg<T, NN>::CB, NN>(kcut);                                               \
-      hipLaunchKernelGGL((k_cols_group<T, NN>), dim3(col_blocks<T, NN>(keep), count), dim3(ColCfg<T, NN>::NT), 0, s, bt, \
-                         keep, Cq, tw);                                                                       \
-    }                                                                                                         \
-    break;
+#define CASE(NN)                                                                                                  \
+  case NN: {                                                                                                      \
+    constexpr int CW = NN == 256 ? narrow_cols<NN>() : ColCfg<T, NN>::CW, NT = NN == 256 ? 64 : ColCfg<T, NN>::NT; \
+    const int keep = tiles_kept<ColCfg<T, NN>::CB, NN>(kcut);                                                     \
+    hipLaunchKernelGGL((k_cols_group<T, NN, CW, NT>), dim3(col_blocks<T, NN, CW>(keep), count), dim3(NT), 0, s,   \
+                       bt, keep, Cq, tw);                                                                         \
+    break;                                                                                                        \
+  }
     AIM_FOR_SIZES(CASE)
 #undef CASE
     default: return AIM_E_ARG;

@@ -3,8 +3,9 @@ the separate kernels (many rows): a product alone against the same column of a
 batch that is past the rule's limit, for FFT lengths 32 .. 512 (1024: never fused), pulses and
 hats (one and three channels), FP64 and FP32 grids, filtered and not; contours
 with few and with many (over 32) contributions per point, and with rows of
-more points than one sweep of a block takes.  Equality is exact: both sum
-the same terms in the same order."""
+more points than one sweep of a block takes.  The column pass of
+the single product takes one-wave blocks for FFT length 512, that of the batch
+wide ones.  Equality is exact: the same terms in the same order."""
 import math
 
 import pytest
