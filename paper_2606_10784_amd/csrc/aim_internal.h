@@ -257,6 +257,16 @@ struct AtMap {
   const void* w[3] = {nullptr, nullptr, nullptr};
 };
 
+// The near-field build gives kNG lanes to an entry, and HIP takes fewer than
+// 2^32 work-items in a launch: entries per launch, a whole number of blocks.
+static constexpr int kNG = 16, kNearBlock = 128;
+static constexpr int64_t kNearLaunch = (int64_t)1 << 26;
+// blocks of the launch that starts at entry q0 of nnz
+inline unsigned near_blocks(int64_t q0, int64_t nnz) {
+  const int64_t cnt = nnz - q0 < kNearLaunch ? nnz - q0 : kNearLaunch, per = kNearBlock / kNG;
+  return (unsigned)((cnt + per - 1) / per);
+}
+
 // kernels / launchers (aim_kernels.hip)
 aim_status dev_alloc(Ctx* c, void** p, size_t bytes);
 aim_status setup_device(Ctx* c);                        // tables, spectrum, near field

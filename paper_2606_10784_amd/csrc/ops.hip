@@ -227,7 +227,6 @@ struct NearGeo {
 // The lanes evaluate the kernel at the quadrature nodes side by side and leave
 // the terms in the group's LDS; every sum is then taken by one lane, term by
 // term in node order, so an entry's value does not depend on the grouping.
-static constexpr int kNG = 16;
 struct NearGroup {
   int l;        // lane within the group
   double* t;    // kNearLds doubles of LDS
@@ -591,7 +590,6 @@ __device__ double2 grid_pair(const NearGroup& g, const double* Wi, const double*
 // 16 384 (5.6), 80 ms for 20 001 hats (28.8).  Bound by FP64 issue in the
 // Bessel functions; two waves per SIMD (the function's own registers would
 // leave one wave per SIMD: 1.6 ms; three or four spill: 1.0 to 1.2 ms).
-static constexpr int kNearBlock = 128;
 __global__ __launch_bounds__(kNearBlock, 2) void k_near_build(
     NearGeo G, int basis, int64_t nnz, const int32_t* __restrict__ rows, const int32_t* __restrict__ cols,
     const int32_t* __restrict__ anx, const int32_t* __restrict__ any, const double* W0, const double* W1,
@@ -1411,12 +1409,14 @@ aim_status setup_device(Ctx* c) {
     TRY(up.send(tmp.p));
     if (nnz > 0) {
       NearGeo G{c->d_vx, c->d_vy, c->d_h, c->d_tx, c->d_ty, N, t.k, d_gl};
-      const int per = kNearBlock / kNG;
       hipLaunchKernelGGL(k_entry_rows, dim3((N + 3) / 4), dim3(256), 0, s, N, c->d_nr_ptr, d_rows);
-      hipLaunchKernelGGL(k_near_build, dim3((unsigned)((nnz + per - 1) / per)), dim3(kNearBlock), 0, s, G, t.basis, nnz,
-                         d_rows, c->d_nr_col, d_anx, d_any, c->d_W[0], c->d_W[1], c->d_W[2], c->d_W[3],
-                         c->d_ksmall, c->ks, c->d_CS, c->d_CN);
-      AIM_HIP_CHECK(hipGetLastError());
+      for (int64_t q0 = 0; q0 < nnz; q0 += kNearLaunch) {
+        hipLaunchKernelGGL(k_near_build, dim3(near_blocks(q0, nnz)), dim3(kNearBlock), 0, s, G, t.basis,
+                           std::min(nnz - q0, kNearLaunch), d_rows + q0, c->d_nr_col + q0, d_anx, d_any, c->d_W[0],
+                           c->d_W[1], c->d_W[2], c->d_W[3], c->d_ksmall, c->ks, c->d_CS + q0,
+                           c->d_CN ? c->d_CN + q0 : nullptr);
+        AIM_HIP_CHECK(hipGetLastError());
+      }
     }
     if (t.band_w >= 0 && nnz > 0) {
       const size_t bb = (size_t)(t.band_w + 1) * N * sizeof(double2);

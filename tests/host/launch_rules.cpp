@@ -1,0 +1,19 @@
+// Host tier of the test suite: prints the launch arithmetic of the device
+// set-up for tests/test_launch_rules.py; host code only.
+//   near NNZ     "q0 blocks" of each launch of the near-field build
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+
+#include "../../paper_2606_10784_amd/csrc/aim_internal.h"
+
+int main(int argc, char** argv) {
+  if (argc == 3 && !std::strcmp(argv[1], "near")) {
+    const int64_t nnz = std::atoll(argv[2]);
+    std::printf("%d %d\n", aim::kNG, aim::kNearBlock);
+    for (int64_t q0 = 0; q0 < nnz; q0 += aim::kNearLaunch)
+      std::printf("%lld %u\n", (long long)q0, aim::near_blocks(q0, nnz));
+    return 0;
+  }
+  return 2;
+}
