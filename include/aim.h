@@ -118,7 +118,8 @@ typedef struct {
                              the smallest power of two >= 2m (n_pad of aim_info) */
   double eps;             /* grid step; grid centred at 0, L = (m-1) eps / 2        */
   int32_t quad;           /* Gauss-Legendre nodes per segment in the stencils (>=1) */
-  int32_t near_radius;    /* anchor Chebyshev radius of the near zone, 3..m-4       */
+  int32_t near_radius;    /* anchor Chebyshev radius of the near zone, 3..m-4; at
+                             most 2^31 - 1 near pairs (AIM_E_ARG past that)      */
   int32_t precision;      /* AIM_FP64 or AIM_MIXED (also builds the FP32 grid data) */
   int32_t max_rhs;        /* largest nrhs of later calls (1..AIM_MAX_RHS)           */
   void* stream;           /* hipStream_t for all device work (NULL: default stream) */

@@ -14,6 +14,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>
+#include <memory>
 
 #include "aim_internal.h"
 
@@ -101,7 +102,8 @@ static inline void lagrange4(double t, double l[4]) {
 // The relation is symmetric: handing out the bases in ascending order fills
 // every row sorted.  Against binary searches and a sort per row, whole tables:
 // 6.5 -> 1.8 ms (3 328 bases, 139 k entries), 43 -> 11 ms (16 384, 1.7 M).
-static void near_zone(HostTables& t) {
+// More entries than the row pointers count are refused before any list is made.
+static aim_status near_zone(HostTables& t) {
   const int N = t.N, m = t.m, R = t.R, D = 2 * R + 1;
   std::vector<int32_t> start(m + 1, 0), byx(N), ord(N);
   for (int j = 0; j < N; ++j) start[t.anc_x[j] + 1]++;
@@ -114,8 +116,12 @@ static void near_zone(HostTables& t) {
     std::vector<int32_t> fill(start.begin(), start.end() - 1);
     for (int q = 0; q < N; ++q) ord[fill[t.anc_y[byx[q]]]++] = byx[q];
   }
-  std::vector<int32_t> range((size_t)N * D * 2, 0);   // [basis][dy]: from, to in ord
+  // [basis][dy]: from, to in ord; calloc, so that cell rows without bases take no memory
+  std::unique_ptr<int32_t, decltype(&std::free)> mem((int32_t*)std::calloc((size_t)N * D * 2, 4), &std::free);
+  int32_t* range = mem.get();
+  if (!range) return AIM_E_OOM;
   t.nr_ptr.assign(N + 1, 0);
+  int64_t total = 0;
   for (int y = 0; y < m; ++y) {
     if (start[y] == start[y + 1]) continue;
     for (int dy = -R; dy <= R; ++dy) {
@@ -131,7 +137,9 @@ static void near_zone(HostTables& t) {
         rg[0] = lo;
         rg[1] = hi;
         t.nr_ptr[i + 1] += hi - lo;
+        total += hi - lo;
       }
+      if (total > INT32_MAX) return AIM_E_ARG;
     }
   }
   for (int i = 0; i < N; ++i) t.nr_ptr[i + 1] += t.nr_ptr[i];
@@ -142,6 +150,7 @@ static void near_zone(HostTables& t) {
       const int32_t* rg = &range[((size_t)j * D + d) * 2];
       for (int q = rg[0]; q < rg[1]; ++q) t.nr_col[fill[ord[q]]++] = j;
     }
+  return AIM_OK;
 }
 
 aim_status build_host_tables(const aim_params* p, HostTables& t, std::string& err) {
@@ -403,7 +412,8 @@ aim_status build_host_tables(const aim_params* p, HostTables& t, std::string& er
     return AIM_OK;
   }
 
-  near_zone(t);
+  const aim_status near = near_zone(t);
+  if (near != AIM_OK) { err = "near pairs"; return near; }
   // Banded symmetric storage of the near field when it pays: bases are
   // numbered along the contour, so near pairs have a small cyclic index
   // distance |i - j|_N <= w, and the near matrices are symmetric (Galerkin,
