@@ -359,9 +359,10 @@ aim_status aim_near_row(aim_ctx ctx, int32_t op, int32_t row, int32_t cap,
    max_samples) is bracketed by a pair of events; aim_profile_stop
    synchronises the stream, returns the mean duration in ms of the sampled
    launches, the number sampled and the number of launches seen, and stops
-   recording.  On small grids the row pass contains the anterpolation: that
-   launch counts for either kernel.  Errors: AIM_E_ARG (kernel id, every < 1), AIM_E_STATE (stop
-   without start), AIM_E_HIP.                                                  */
+   recording.  Small grids take the anterpolation inside the forward row pass;
+   while either of the two is timed they run apart, with the same values.
+   Errors: AIM_E_ARG (kernel id, every < 1), AIM_E_STATE (stop without start),
+   AIM_E_HIP.                                                                  */
 enum { AIM_K_ANTERP = 0, AIM_K_ROWS_FWD = 1, AIM_K_COLS = 2, AIM_K_ROWS_INV = 3, AIM_K_INTERP = 4 };
 aim_status aim_profile_start(aim_ctx ctx, int32_t kernel, int32_t every, int32_t max_samples);
 aim_status aim_profile_stop(aim_ctx ctx, double* avg_ms, int64_t* samples, int64_t* launches);

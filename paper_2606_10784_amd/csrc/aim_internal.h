@@ -257,6 +257,20 @@ struct AtMap {
   const void* w[3] = {nullptr, nullptr, nullptr};
 };
 
+// Whether pass 1 takes the anterpolation along: the whole launch is on the chip
+// at once.  Whole products, separate / fused in us, by rows times pairs:
+//   FP64  n = 128:  56  20.5 / 18.7   448  25.2 / 24.1   1344  40.8 / 41.5
+//         n = 512: 214  22.0 / 21.0   856  31.2 / 31.0   1712  47.4 / 48.0
+//   FP32  n = 512: 214  21.8 / 20.8  1284  30.3 / 29.3   2568  45.3 / 45.9
+// From n = 1024 on a block of 256 threads is compiled to other fused multiply-
+// adds than the separate kernel (a column would depend on its batch), and one
+// of as many threads as that kernel's is slower (28.7 / 33.4).
+// While either kernel is timed (aim_profile_start) they stay apart: the same values.
+inline bool anterp_in_rows(int n, bool f32, int nr, int pairs, int prof_kernel) {
+  if (prof_kernel == AIM_K_ANTERP || prof_kernel == AIM_K_ROWS_FWD) return false;
+  return n <= 512 && (int64_t)nr * pairs <= (f32 ? 1536 : 768);
+}
+
 // The near-field build gives kNG lanes to an entry, and HIP takes fewer than
 // 2^32 work-items in a launch: entries per launch, a whole number of blocks.
 static constexpr int kNG = 16, kNearBlock = 128;

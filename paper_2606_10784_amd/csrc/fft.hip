@@ -1299,18 +1299,6 @@ aim_status launch_rows_fwd(int n, const cplx<T>* U, int n_act, const int32_t* ro
   return hipGetLastError() == hipSuccess ? AIM_OK : AIM_E_HIP;
 }
 
-// Whether pass 1 takes the anterpolation along: the whole launch is on the chip
-// at once.  Whole products, separate / fused in us, by rows times pairs:
-//   FP64  n = 128:  56  20.5 / 18.7   448  25.2 / 24.1   1344  40.8 / 41.5
-//         n = 512: 214  22.0 / 21.0   856  31.2 / 31.0   1712  47.4 / 48.0
-//   FP32  n = 512: 214  21.8 / 20.8  1284  30.3 / 29.3   2568  45.3 / 45.9
-// From n = 1024 on a block of 256 threads is compiled to other fused multiply-
-// adds than the separate kernel (a column would depend on its batch), and one
-// of as many threads as that kernel's is slower (28.7 / 33.4).
-bool rows_fwd_at_fits(int n, bool f32, int nr, int pairs) {
-  return n <= 512 && (int64_t)nr * pairs <= (f32 ? 1536 : 768);
-}
-
 template <typename T, typename TW>
 aim_status launch_rows_fwd_at(int n, const AtMap& at, const double2* x, int64_t ldx, int nrhs, const int32_t* row_ptr,
                               const int32_t* act_ix, int nr, int ldt, int kcut, int pairs, cplx<T>* Tb,

@@ -29,7 +29,6 @@ template <typename T, typename TW>
 aim_status launch_rows_fwd_at(int n, const AtMap& at, const double2* x, int64_t ldx, int nrhs, const int32_t* row_ptr,
                               const int32_t* act_ix, int nr, int ldt, int kcut, int pairs, cplx<T>* Tb,
                               const cplx<T>* tw, hipStream_t s);
-bool rows_fwd_at_fits(int n, bool f32, int nr, int pairs);
 bool rows_few_columns(int n, bool f32, int kcut, int n_act, int nr);
 template <typename T>
 aim_status launch_rows_inv(int n, const cplx<T>* Tb, int nr, int ldt, int kcut, const int32_t* row_ptr,
@@ -1586,13 +1585,11 @@ static aim_status grid_pre(Ctx* c, const int* chans, int nch, bool filt, int nrh
   cplx<T>* Tb = (cplx<T>*)c->d_T;
   const bool f32 = sizeof(T) == 4;
   const int kcut = grid_kcut(c, filt);
-  if (rows_fwd_at_fits(t.n, f32, t.nr, pairs) && !rows_few_columns(t.n, f32, kcut, t.n_act, t.nr)) {
+  if (anterp_in_rows(t.n, f32, t.nr, pairs, c->prof_kernel) && !rows_few_columns(t.n, f32, kcut, t.n_act, t.nr)) {
     AtMap at;
     at.ptr = c->d_at_ptr;
     at.basis = c->d_at_basis;
     for (int q = 0; q < nch; ++q) at.w[q] = f32 ? (const void*)c->d_at_wf[chans[q]] : (const void*)c->d_at_w[chans[q]];
-    ProfScope pa(c, AIM_K_ANTERP);   // one launch for both: it counts as either
-    ProfScope pr(c, AIM_K_ROWS_FWD);
     return launch_rows_fwd_at<T, T>(t.n, at, x, ldx, nrhs, c->d_row_ptr, c->d_act_ix, t.nr, tile_rows(t.nr), kcut,
                                     pairs, Tb, grid_twiddles<T>(c), s);
   }

@@ -1,6 +1,8 @@
-// Host tier of the test suite: prints the launch arithmetic of the device
-// set-up for tests/test_launch_rules.py; host code only.
-//   near NNZ     "q0 blocks" of each launch of the near-field build
+// Host tier of the test suite: prints the launch arithmetic and the dispatch
+// rules of the library for tests/test_launch_rules.py; host code only.
+//   near NNZ                "q0 blocks" of each launch of the near-field build
+//   fused N F32 NR PAIRS K  whether the row pass takes the anterpolation along
+//                           while pipeline kernel K is timed (-1: none)
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -13,6 +15,11 @@ int main(int argc, char** argv) {
     std::printf("%d %d\n", aim::kNG, aim::kNearBlock);
     for (int64_t q0 = 0; q0 < nnz; q0 += aim::kNearLaunch)
       std::printf("%lld %u\n", (long long)q0, aim::near_blocks(q0, nnz));
+    return 0;
+  }
+  if (argc == 7 && !std::strcmp(argv[1], "fused")) {
+    std::printf("%d\n", (int)aim::anterp_in_rows(std::atoi(argv[2]), std::atoi(argv[3]) != 0, std::atoi(argv[4]),
+                                                 std::atoi(argv[5]), std::atoi(argv[6])));
     return 0;
   }
   return 2;

@@ -1,5 +1,5 @@
-"""Host tier: launch arithmetic of the library (csrc/aim_internal.h, built with
-g++), checked on the CPU at the limits HIP sets."""
+"""Host tier: launch arithmetic and dispatch rules of the library
+(csrc/aim_internal.h, built with g++), checked on the CPU at their limits."""
 import os
 import subprocess
 
@@ -36,3 +36,11 @@ def test_near_build_launches(rules, nnz):
         assert 0 < blocks * block < 2**32
         end = q0 + blocks * per
     assert nnz <= end < nnz + per
+
+
+@pytest.mark.parametrize("f32,limit", [(0, 768), (1, 1536)])
+def test_timed_kernels_run_apart(rules, f32, limit):
+    """The forward row pass takes the anterpolation along up to its limit of rows, except while one of the two is timed."""
+    for n, rows, fused in ((128, limit, 1), (512, limit, 1), (512, limit + 1, 0), (1024, 8, 0)):
+        for kernel in range(-1, 5):
+            assert rules("fused", n, f32, rows, 1, kernel) == [[fused if kernel not in (0, 1) else 0]]
