@@ -271,6 +271,33 @@ inline bool anterp_in_rows(int n, bool f32, int nr, int pairs, int prof_kernel) 
   return n <= 512 && (int64_t)nr * pairs <= (f32 ? 1536 : 768);
 }
 
+// Row passes over the tiles that a cut spectrum keeps (pk pairs of columns and
+// column 0): sums over the kept columns where these cost less than FFTs of the
+// rows.  The sums take pk n_act steps, the FFTs nr n (log); whole products,
+// FFTs / sums in us, for one right-hand side, 4 and 24, by pk n_act / (nr n):
+//   FP64  n = 1024:  .15  22.1 / 19.1   24.1 / 29.2   55 / 43
+//                    .59  22.0 / 19.7   24.8 / 31.6   67 / 57
+//         n = 2048:  .15  25.0 / 21.0   38.2 / 36.1   129 / 62
+//                    .59  25.0 / 23.7   44.0 / 47.6   151 / 100
+//         n = 4096:  .15  41.9 / 27.7   108 / 58      545 / 141
+//                    .60  47.7 / 47.7   130 / 105     659 / 353
+//   FP32  n = 1024:  .59  21.9 / 19.4   23.8 / 27.7   42 / 40
+//         n = 2048:  .59  22.7 / 22.6   29.5 / 34.6   89 / 69
+//         n = 4096:  .15  30.2 / 26.0   59 / 45       263 / 100
+//                    .60  32.0 / 37.9   74 / 74       324 / 216
+// (64 right-hand sides, FP64, n = 2048: .65 113 / 86, .98 120 / 104).  At n = 512
+// they gain 8 % for 24 right-hand sides and lose 28 % for 4 (.13: 18.7 / 18.9,
+// 20.8 / 26.6, 36.6 / 33.4), below it they lose throughout.  The rule does not
+// look at the batch: a column's bits do not depend on it.  n / 16 pairs is what
+// the LDS of the inverse sums holds for four right-hand sides (33 KB at n = 4096);
+// it cuts off contours of fewer than 9.6 points a row.
+// Error of a product (rms over y, against 80-bit arithmetic), FFTs / sums: FP32
+// 3.9e-7 / 2.9e-7 (n = 4096), 3.4e-7 / 2.6e-7 (n = 2048), 3.4e-7 / 2.8e-7
+// (n = 1024); FP64 equal to 1 % (the kernel samples' rounding carries it).
+inline bool few_columns_pay(int n, int pk, int n_act, int nr) {
+  return n >= 1024 && pk <= n / 16 && 5 * (int64_t)pk * n_act <= 3 * (int64_t)n * nr;
+}
+
 // The near-field build gives kNG lanes to an entry, and HIP takes fewer than
 // 2^32 work-items in a launch: entries per launch, a whole number of blocks.
 static constexpr int kNG = 16, kNearBlock = 128;

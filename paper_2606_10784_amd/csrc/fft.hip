@@ -1214,19 +1214,11 @@ __global__ __launch_bounds__(NT) void k_cols_group(ColBatch batch, int keep,
 // ---------------------------------------------------------------------------
 #define AIM_FOR_SIZES(X) X(32) X(64) X(128) X(256) X(512) X(1024) X(2048) X(4096)
 
-// Row passes over the tiles a spectrum cut at kcut keeps: sums over the kept
-// columns where these cost less than FFTs of the rows.  The sums take pk n_act
-// steps, the FFTs nr N (log); whole products, FFTs / sums in us, for one
-// right-hand side and a batch, by pk n_act / (nr N):
-//   n = 2048:  .35  25.7 / 22.0, 237 / 129    .52  26.6 / 23.8, 256 / 159
-//              .65  30.4 / 30.4, 113 / 86     .98  31.2 / 34.8, 120 / 104
-//   n = 1024:  .47  22.9 / 22.1,  60 / 53     .94  23.3 / 23.2,  66 / 63
-// Below n = 512 the FFTs are as short as a row's sums (n = 128: 36 / 39).  Past
-// N / 16 pairs (LDS of the inverse sums) no contour meets the rule.
+// kept pairs of columns, and whether the row passes sum them (few_columns_pay)
 template <typename T, int N>
 bool rows_few(int kcut, int n_act, int nr, int& pk) {
   pk = tiles_kept<ColCfg<T, N>::CB, N>(kcut) * (ColCfg<T, N>::CB / 2);
-  return N >= 512 && pk <= N / 16 && 5 * (int64_t)pk * n_act <= 3 * (int64_t)N * nr;
+  return few_columns_pay(N, pk, n_act, nr);
 }
 template <typename T> bool rows_few_n(int n, int kcut, int n_act, int nr) {
   int pk;

@@ -3,6 +3,7 @@
 //   near NNZ                "q0 blocks" of each launch of the near-field build
 //   fused N F32 NR PAIRS K  whether the row pass takes the anterpolation along
 //                           while pipeline kernel K is timed (-1: none)
+//   few N PK NACT NR        whether the row passes sum over PK kept pairs of columns
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -20,6 +21,11 @@ int main(int argc, char** argv) {
   if (argc == 7 && !std::strcmp(argv[1], "fused")) {
     std::printf("%d\n", (int)aim::anterp_in_rows(std::atoi(argv[2]), std::atoi(argv[3]) != 0, std::atoi(argv[4]),
                                                  std::atoi(argv[5]), std::atoi(argv[6])));
+    return 0;
+  }
+  if (argc == 6 && !std::strcmp(argv[1], "few")) {
+    std::printf("%d\n", (int)aim::few_columns_pay(std::atoi(argv[2]), std::atoi(argv[3]), std::atoi(argv[4]),
+                                                  std::atoi(argv[5])));
     return 0;
   }
   return 2;

@@ -44,3 +44,15 @@ def test_timed_kernels_run_apart(rules, f32, limit):
     for n, rows, fused in ((128, limit, 1), (512, limit, 1), (512, limit + 1, 0), (1024, 8, 0)):
         for kernel in range(-1, 5):
             assert rules("fused", n, f32, rows, 1, kernel) == [[fused if kernel not in (0, 1) else 0]]
+
+
+def test_few_columns_rule(rules):
+    """Sums over the kept columns only from n = 1024, up to n / 16 pairs and 3/5 of the FFTs' steps."""
+    for n in (32, 256, 512):
+        assert rules("few", n, 1, 10 * n, n) == [[0]]
+    for n in (1024, 2048, 4096):
+        assert rules("few", n, n // 16, 9 * n // 4, n // 4) == [[1]]        # 9 points a row: n / 16 binds
+        assert rules("few", n, n // 16 + 1, 9 * n // 4, n // 4) == [[0]]
+        assert rules("few", n, n // 25, 15 * n // 4, n // 4) == [[1]]       # 15 points a row: pk <= n / 25
+        assert rules("few", n, n // 25 + 1, 15 * n // 4, n // 4) == [[0]]
+    assert rules("few", 4096, 256, 2**20, 2048) == [[0]]                    # products past 32 bits
