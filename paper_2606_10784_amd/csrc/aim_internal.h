@@ -294,8 +294,9 @@ inline bool anterp_in_rows(int n, bool f32, int nr, int pairs, int prof_kernel) 
 // Error of a product (rms over y, against 80-bit arithmetic), FFTs / sums: FP32
 // 3.9e-7 / 2.9e-7 (n = 4096), 3.4e-7 / 2.6e-7 (n = 2048), 3.4e-7 / 2.8e-7
 // (n = 1024); FP64 equal to 1 % (the kernel samples' rounding carries it).
+static constexpr int kFewLength = 1024;   // no kernels for the sums below it
 inline bool few_columns_pay(int n, int pk, int n_act, int nr) {
-  return n >= 1024 && pk <= n / 16 && 5 * (int64_t)pk * n_act <= 3 * (int64_t)n * nr;
+  return n >= kFewLength && pk <= n / 16 && 5 * (int64_t)pk * n_act <= 3 * (int64_t)n * nr;
 }
 
 // The near-field build gives kNG lanes to an entry, and HIP takes fewer than

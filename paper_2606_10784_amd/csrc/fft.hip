@@ -1239,16 +1239,20 @@ void rows_fwd(const cplx<T>* U, int n_act, const int32_t* row_ptr, const int32_t
   const unsigned rows = 8 * ((nr + 7) / 8);
   const dim3 g(rows, pairs), b(row_threads<N>());
   const int keep = tiles_kept<ColCfg<T, N>::CB, N>(kcut);
-  int pk;
-  if (rows_few<T, N>(kcut, n_act, nr, pk)) {
-    const int kc = pk / kFewCols + 1;
-    if (pairs < kFewPairs)
-      hipLaunchKernelGGL((k_rows_fwd_few<T, N, 1>), dim3(rows, pairs, kc), dim3(64), 0, s, U, n_act, row_ptr, act_ix, nr, ldt, pk,
-                         pairs, Tb, tw);
-    else
-      hipLaunchKernelGGL((k_rows_fwd_few<T, N, kFewPairs>), dim3(rows, (pairs + kFewPairs - 1) / kFewPairs, kc),
-                         dim3(64), 0, s, U, n_act, row_ptr, act_ix, nr, ldt, pk, pairs, Tb, tw);
-  } else if (keep == N / ColCfg<T, N>::CB - 1) {
+  if constexpr (N >= kFewLength) {
+    int pk;
+    if (rows_few<T, N>(kcut, n_act, nr, pk)) {
+      const int kc = pk / kFewCols + 1;
+      if (pairs < kFewPairs)
+        hipLaunchKernelGGL((k_rows_fwd_few<T, N, 1>), dim3(rows, pairs, kc), dim3(64), 0, s, U, n_act, row_ptr, act_ix,
+                           nr, ldt, pk, pairs, Tb, tw);
+      else
+        hipLaunchKernelGGL((k_rows_fwd_few<T, N, kFewPairs>), dim3(rows, (pairs + kFewPairs - 1) / kFewPairs, kc),
+                           dim3(64), 0, s, U, n_act, row_ptr, act_ix, nr, ldt, pk, pairs, Tb, tw);
+      return;
+    }
+  }
+  if (keep == N / ColCfg<T, N>::CB - 1) {
     hipLaunchKernelGGL((k_rows_fwd<T, N, false>), g, b, 0, s, U, n_act, row_ptr, act_ix, nr, ldt, keep, Tb, tw);
   } else {
     hipLaunchKernelGGL((k_rows_fwd<T, N, true>), g, b, 0, s, U, n_act, row_ptr, act_ix, nr, ldt, keep, Tb, tw);
@@ -1260,16 +1264,21 @@ void rows_inv(const cplx<T>* Tb, int nr, int ldt, int kcut, const int32_t* row_p
   const unsigned rows = 8 * ((nr + 7) / 8);
   const dim3 g(rows, pairs), b(row_threads<N>());
   const int keep = tiles_kept<ColCfg<T, N>::CB, N>(kcut);
-  int pk;
-  if (rows_few<T, N>(kcut, n_act, nr, pk)) {
-    const size_t lds = 2 * (size_t)(pk + 1) * sizeof(cplx<T>);
-    if (pairs < kFewPairs)
-      hipLaunchKernelGGL((k_rows_inv_few<T, N, 1>), g, dim3(few_inv_threads<1>()), lds, s, Tb, nr, ldt, pk, pairs, row_ptr,
-                         act_ix, V, n_act, tw);
-    else
-      hipLaunchKernelGGL((k_rows_inv_few<T, N, kFewPairs>), dim3(rows, (pairs + kFewPairs - 1) / kFewPairs),
-                         dim3(few_inv_threads<kFewPairs>()), kFewPairs * lds, s, Tb, nr, ldt, pk, pairs, row_ptr, act_ix, V, n_act, tw);
-  } else if (keep == N / ColCfg<T, N>::CB - 1) {
+  if constexpr (N >= kFewLength) {
+    int pk;
+    if (rows_few<T, N>(kcut, n_act, nr, pk)) {
+      const size_t lds = 2 * (size_t)(pk + 1) * sizeof(cplx<T>);
+      if (pairs < kFewPairs)
+        hipLaunchKernelGGL((k_rows_inv_few<T, N, 1>), g, dim3(few_inv_threads<1>()), lds, s, Tb, nr, ldt, pk, pairs,
+                           row_ptr, act_ix, V, n_act, tw);
+      else
+        hipLaunchKernelGGL((k_rows_inv_few<T, N, kFewPairs>), dim3(rows, (pairs + kFewPairs - 1) / kFewPairs),
+                           dim3(few_inv_threads<kFewPairs>()), kFewPairs * lds, s, Tb, nr, ldt, pk, pairs, row_ptr,
+                           act_ix, V, n_act, tw);
+      return;
+    }
+  }
+  if (keep == N / ColCfg<T, N>::CB - 1) {
     hipLaunchKernelGGL((k_rows_inv<T, N, false>), g, b, 0, s, Tb, nr, ldt, keep, row_ptr, act_ix, V, n_act, tw);
   } else {
     hipLaunchKernelGGL((k_rows_inv<T, N, true>), g, b, 0, s, Tb, nr, ldt, keep, row_ptr, act_ix, V, n_act, tw);
