@@ -26,6 +26,7 @@
 #include <hip/hip_ext.h>
 
 #include "aim_internal.h"
+#include "wave.h"
 
 namespace aim {
 
@@ -424,13 +425,6 @@ __device__ __forceinline__ void ct_pass(cplx<T>* buf, const cplx<T>* __restrict_
   __syncthreads();
 }
 
-// LDS values that the lanes of one wave exchange: order, no barrier
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // ct_pass with the base twiddle of each of the thread's butterflies given
 // (w[q] for butterfly tid + q NT, forward sign)
 template <typename T, int N, int NCOL, int NT, bool INV, int S, int R, bool WAVE>
@@ -661,7 +655,7 @@ __global__ __launch_bounds__(row_threads<N>()) void k_rows_fwd(
 // loads (row, point, entry, value).  The FFT leaves most of the block's threads
 // idle, so launches of many rows are better off with the separate kernels.
 static constexpr int kAtThreads = 256;
-template <typename T, typename TW, int N, bool CUT>
+template <typename T, int N, bool CUT>
 __global__ __launch_bounds__(kAtThreads) void k_rows_fwd_at(AtMap at, const double2* __restrict__ x, int64_t ldx,
                                                             int nrhs, const int32_t* __restrict__ row_ptr,
                                                             const int32_t* __restrict__ act_ix, int nr, int ldt,
@@ -679,7 +673,7 @@ __global__ __launch_bounds__(kAtThreads) void k_rows_fwd_at(AtMap at, const doub
   chain_tw<T, N, NT, 16, N, false>(tw, wt);
   for (int i = tid; i < N / 2; i += NT) buf[pidx(i)] = mk<T>(0, 0);
   __syncthreads();
-  const TW* w = (const TW*)(ch == 0 ? at.w[0] : (ch == 1 ? at.w[1] : at.w[2]));
+  const T* w = (const T*)(ch == 0 ? at.w[0] : (ch == 1 ? at.w[1] : at.w[2]));
   const double2* xr = x + (size_t)(pair - ch * nrhs) * ldx;
   for (int a = a0 + (tid >> 4); a < a1; a += NG * GU) {
     int e[GU], e1[GU], ix[GU];
@@ -704,7 +698,7 @@ __global__ __launch_bounds__(kAtThreads) void k_rows_fwd_at(AtMap at, const doub
         for (int h = 0; h < 2; ++h)
           if (e[u] + 16 * h < e1[u]) {
             b[u][h] = at.basis[e[u] + 16 * h];
-            we[u][h] = (T)w[e[u] + 16 * h];
+            we[u][h] = w[e[u] + 16 * h];
           }
 #pragma unroll
       for (int u = 0; u < GU; ++u) {
@@ -1300,7 +1294,7 @@ aim_status launch_rows_fwd(int n, const cplx<T>* U, int n_act, const int32_t* ro
   return hipGetLastError() == hipSuccess ? AIM_OK : AIM_E_HIP;
 }
 
-template <typename T, typename TW>
+template <typename T>
 aim_status launch_rows_fwd_at(int n, const AtMap& at, const double2* x, int64_t ldx, int nrhs, const int32_t* row_ptr,
                               const int32_t* act_ix, int nr, int ldt, int kcut, int pairs, cplx<T>* Tb,
                               const cplx<T>* tw, hipStream_t s) {
@@ -1311,10 +1305,10 @@ aim_status launch_rows_fwd_at(int n, const AtMap& at, const double2* x, int64_t 
   case NN: {                                                                                                          \
     const int keep = tiles_kept<ColCfg<T, NN>::CB, NN>(kcut);                                                         \
     if (keep == NN / ColCfg<T, NN>::CB - 1)                                                                           \
-      hipLaunchKernelGGL((k_rows_fwd_at<T, TW, NN, false>), g, b, 0, s, at, x, ldx, nrhs, row_ptr, act_ix, nr, ldt,   \
+      hipLaunchKernelGGL((k_rows_fwd_at<T, NN, false>), g, b, 0, s, at, x, ldx, nrhs, row_ptr, act_ix, nr, ldt,   \
                          keep, Tb, tw);                                                                               \
     else                                                                                                              \
-      hipLaunchKernelGGL((k_rows_fwd_at<T, TW, NN, true>), g, b, 0, s, at, x, ldx, nrhs, row_ptr, act_ix, nr, ldt,    \
+      hipLaunchKernelGGL((k_rows_fwd_at<T, NN, true>), g, b, 0, s, at, x, ldx, nrhs, row_ptr, act_ix, nr, ldt,    \
                          keep, Tb, tw);                                                                               \
     break;                                                                                                            \
   }
@@ -1440,10 +1434,10 @@ template aim_status launch_rows_fwd<double>(int, const double2*, int, const int3
                                             double2*, const double2*, hipStream_t);
 template aim_status launch_rows_fwd<float>(int, const float2*, int, const int32_t*, const int32_t*, int, int, int, int,
                                            float2*, const float2*, hipStream_t);
-template aim_status launch_rows_fwd_at<double, double>(int, const AtMap&, const double2*, int64_t, int, const int32_t*,
+template aim_status launch_rows_fwd_at<double>(int, const AtMap&, const double2*, int64_t, int, const int32_t*,
                                                       const int32_t*, int, int, int, int, double2*, const double2*,
                                                       hipStream_t);
-template aim_status launch_rows_fwd_at<float, float>(int, const AtMap&, const double2*, int64_t, int, const int32_t*,
+template aim_status launch_rows_fwd_at<float>(int, const AtMap&, const double2*, int64_t, int, const int32_t*,
                                                     const int32_t*, int, int, int, int, float2*, const float2*,
                                                     hipStream_t);
 template aim_status launch_rows_inv<double>(int, const double2*, int, int, int, const int32_t*, const int32_t*, int,

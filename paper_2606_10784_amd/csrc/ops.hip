@@ -18,6 +18,7 @@
 #include <utility>
 
 #include "aim_internal.h"
+#include "wave.h"
 
 namespace aim {
 
@@ -25,7 +26,7 @@ template <typename T>
 aim_status launch_rows_fwd(int n, const cplx<T>* U, int n_act, const int32_t* row_ptr,
                            const int32_t* act_ix, int nr, int ldt, int kcut, int pairs, cplx<T>* Tb,
                            const cplx<T>* tw, hipStream_t s);
-template <typename T, typename TW>
+template <typename T>
 aim_status launch_rows_fwd_at(int n, const AtMap& at, const double2* x, int64_t ldx, int nrhs, const int32_t* row_ptr,
                               const int32_t* act_ix, int nr, int ldt, int kcut, int pairs, cplx<T>* Tb,
                               const cplx<T>* tw, hipStream_t s);
@@ -234,17 +235,11 @@ static constexpr int kNearTerms = 7 * 32;             // terms of one quadrature
 static constexpr int kMaxPsiBreaks = 128;
 static constexpr int kNearLds = kNearTerms + 8 + kMaxPsiBreaks;
 
-__device__ __forceinline__ void group_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // sums held by the lanes 0..7 -> every lane: v[k] = lane k's acc
 __device__ __forceinline__ void group_share(const NearGroup& g, double acc, double* v) {
-  group_sync();
+  wave_sync();
   if (g.l < 8) g.t[kNearTerms + g.l] = acc;
-  group_sync();
+  wave_sync();
   for (int k = 0; k < 8; ++k) v[k] = g.t[kNearTerms + k];
 }
 
@@ -284,7 +279,7 @@ __device__ void moments_self(const NearGroup& g, const NearGeo& G, double h, dou
     t[3] = F.x;
     t[4] = F.y;
   }
-  group_sync();
+  wave_sync();
   double acc = 0.0, v[8];
   if (g.l < 6)   // F00.x, F00.y, F10.x, F10.y, F11.x, F11.y
     for (int i = 0; i < 24; ++i) acc += g.t[5 * i + (g.l >> 1)] * g.t[5 * i + 3 + (g.l & 1)];
@@ -370,7 +365,7 @@ __device__ void moments_adjacent(const NearGroup& g, const NearGeo& G, int a, in
   int nbp = 0;
   if (g.l == 0) nbp = psi_breaks(psid, cab, bp);
   nbp = __shfl(nbp, 0, kNG);
-  group_sync();
+  wave_sync();
   double accB = 0.0;   // lanes 0..3: B_00, B_10, B_01, B_11
   for (int pnl = 0; pnl + 1 < nbp; ++pnl) {
     const double lo = bp[pnl], hi = bp[pnl + 1];
@@ -409,12 +404,12 @@ __device__ void moments_adjacent(const NearGroup& g, const NearGeo& G, int a, in
       t[5] = Sd[1];
       t[6] = Sd[2];
     }
-    group_sync();
+    wave_sync();
     if (g.l < 4) {
       const int d = 4 + (g.l == 0 ? 0 : (g.l == 3 ? 2 : 1));
       for (int q = 0; q < 32; ++q) accB += g.t[7 * q + g.l] * g.t[7 * q + d];
     }
-    group_sync();
+    wave_sync();
   }
   double v[8];
   group_share(g, accB, v);
@@ -426,7 +421,7 @@ __device__ void moments_adjacent(const NearGroup& g, const NearGeo& G, int a, in
   for (int i = 0; i < 16; ++i) {
     const double S = x16[i] * ha;
     const double tau = t0 + t1 * S;
-    group_sync();
+    wave_sync();
     {
       const int j = g.l;
       const double Sp = x16[j] * hb;
@@ -443,7 +438,7 @@ __device__ void moments_adjacent(const NearGroup& g, const NearGeo& G, int a, in
       t[4] = f.x;
       t[5] = f.y;
     }
-    group_sync();
+    wave_sync();
     if (g.l < 8)
       for (int j = 0; j < 16; ++j) accF += g.t[6 * j + (g.l >> 1)] * g.t[6 * j + 4 + (g.l & 1)];
   }
@@ -517,7 +512,7 @@ __device__ void moments_disjoint(const NearGroup& g, const NearGeo& G, int a, in
       continue;
     }
     const double wt = t1 - t0, ws = s1 - s0;
-    group_sync();
+    wave_sync();
     {
       const int i = g.l;
       const double ti = t0 + wt * x16[i];
@@ -540,7 +535,7 @@ __device__ void moments_disjoint(const NearGroup& g, const NearGeo& G, int a, in
       t[4] = r1.x;
       t[5] = r1.y;
     }
-    group_sync();
+    wave_sync();
     if (g.l < 8)
       for (int i = 0; i < 16; ++i) acc += g.t[6 * i + (g.l >> 2)] * g.t[6 * i + 2 + (g.l & 3)];
   }
@@ -571,10 +566,10 @@ __device__ double2 grid_pair(const NearGroup& g, const double* Wi, const double*
     inner.x += Wj[f] * kv.x;
     inner.y += Wj[f] * kv.y;
   }
-  group_sync();
+  wave_sync();
   g.t[2 * e] = inner.x;
   g.t[2 * e + 1] = inner.y;
-  group_sync();
+  wave_sync();
   double acc = 0.0, v[8];
   if (g.l < 2)
     for (int q = 0; q < 16; ++q) acc += Wi[q] * g.t[2 * q + g.l];
@@ -1590,7 +1585,7 @@ static aim_status grid_pre(Ctx* c, const int* chans, int nch, bool filt, int nrh
     at.ptr = c->d_at_ptr;
     at.basis = c->d_at_basis;
     for (int q = 0; q < nch; ++q) at.w[q] = f32 ? (const void*)c->d_at_wf[chans[q]] : (const void*)c->d_at_w[chans[q]];
-    return launch_rows_fwd_at<T, T>(t.n, at, x, ldx, nrhs, c->d_row_ptr, c->d_act_ix, t.nr, tile_rows(t.nr), kcut,
+    return launch_rows_fwd_at<T>(t.n, at, x, ldx, nrhs, c->d_row_ptr, c->d_act_ix, t.nr, tile_rows(t.nr), kcut,
                                     pairs, Tb, grid_twiddles<T>(c), s);
   }
   // a single rhs keeps one sum per lane; batches share the entry loads
