@@ -360,7 +360,8 @@ aim_status aim_near_row(aim_ctx ctx, int32_t op, int32_t row, int32_t cap,
    synchronises the stream, returns the mean duration in ms of the sampled
    launches, the number sampled and the number of launches seen, and stops
    recording.  Small grids take the anterpolation inside the forward row pass;
-   while either of the two is timed they run apart, with the same values.
+   a product in which either of the two is sampled runs them apart, with the
+   same values.
    Errors: AIM_E_ARG (kernel id, every < 1), AIM_E_STATE (stop without start),
    AIM_E_HIP.                                                                  */
 enum { AIM_K_ANTERP = 0, AIM_K_ROWS_FWD = 1, AIM_K_COLS = 2, AIM_K_ROWS_INV = 3, AIM_K_INTERP = 4 };

@@ -236,11 +236,15 @@ struct ProfScope {
   bool on = false, attach = false;
   int slot = -1;
   ProfScope(Ctx* cc, int kid, bool attach_events = false) : c(cc), attach(attach_events) {
-    if (c->prof_kernel != kid) return;
-    const int64_t n = c->prof_launches++;
-    if (n % c->prof_every != 0 || c->ev_used >= c->prof_max) return;
+    const bool sampled = due(c, kid);
+    if (c->prof_kernel == kid) ++c->prof_launches;
+    if (!sampled) return;
     slot = c->ev_used++;
     on = attach || hipEventRecord(c->ev0[slot], c->stream) == hipSuccess;
+  }
+  // whether the next launch of kernel `kid` is a sampled one
+  static bool due(const Ctx* c, int kid) {
+    return c->prof_kernel == kid && c->prof_launches % c->prof_every == 0 && c->ev_used < c->prof_max;
   }
   hipEvent_t start() const { return on && attach ? c->ev0[slot] : nullptr; }
   hipEvent_t stop() const { return on && attach ? c->ev1[slot] : nullptr; }
@@ -265,10 +269,9 @@ struct AtMap {
 // From n = 1024 on a block of 256 threads is compiled to other fused multiply-
 // adds than the separate kernel (a column would depend on its batch), and one
 // of as many threads as that kernel's is slower (28.7 / 33.4).
-// While either kernel is timed (aim_profile_start) they stay apart: the same values.
-inline bool anterp_in_rows(int n, bool f32, int nr, int pairs, int prof_kernel) {
-  if (prof_kernel == AIM_K_ANTERP || prof_kernel == AIM_K_ROWS_FWD) return false;
-  return n <= 512 && (int64_t)nr * pairs <= (f32 ? 1536 : 768);
+// A product in which one of the two is timed keeps them apart: the same values.
+inline bool anterp_in_rows(int n, bool f32, int nr, int pairs, bool timed) {
+  return !timed && n <= 512 && (int64_t)nr * pairs <= (f32 ? 1536 : 768);
 }
 
 // Row passes over the tiles that a cut spectrum keeps (pk pairs of columns and

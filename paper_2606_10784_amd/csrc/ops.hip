@@ -1580,11 +1580,13 @@ static aim_status grid_pre(Ctx* c, const int* chans, int nch, bool filt, int nrh
   cplx<T>* Tb = (cplx<T>*)c->d_T;
   const bool f32 = sizeof(T) == 4;
   const int kcut = grid_kcut(c, filt);
-  if (anterp_in_rows(t.n, f32, t.nr, pairs, c->prof_kernel) && !rows_few_columns(t.n, f32, kcut, t.n_act, t.nr)) {
+  const bool timed = ProfScope::due(c, AIM_K_ANTERP) || ProfScope::due(c, AIM_K_ROWS_FWD);
+  if (anterp_in_rows(t.n, f32, t.nr, pairs, timed) && !rows_few_columns(t.n, f32, kcut, t.n_act, t.nr)) {
     AtMap at;
     at.ptr = c->d_at_ptr;
     at.basis = c->d_at_basis;
     for (int q = 0; q < nch; ++q) at.w[q] = f32 ? (const void*)c->d_at_wf[chans[q]] : (const void*)c->d_at_w[chans[q]];
+    ProfScope pa(c, AIM_K_ANTERP), pr(c, AIM_K_ROWS_FWD);   // counted, not timed
     return launch_rows_fwd_at<T>(t.n, at, x, ldx, nrhs, c->d_row_ptr, c->d_act_ix, t.nr, tile_rows(t.nr), kcut,
                                     pairs, Tb, grid_twiddles<T>(c), s);
   }

@@ -1,8 +1,8 @@
 // Host tier of the test suite: prints the launch arithmetic and the dispatch
 // rules of the library for tests/test_launch_rules.py; host code only.
 //   near NNZ                "q0 blocks" of each launch of the near-field build
-//   fused N F32 NR PAIRS K  whether the row pass takes the anterpolation along
-//                           while pipeline kernel K is timed (-1: none)
+//   fused N F32 NR PAIRS T  whether the row pass takes the anterpolation along
+//                           in a product that times (T = 1) one of the two
 //   few N PK NACT NR        whether the row passes sum over PK kept pairs of columns
 #include <cstdio>
 #include <cstdlib>
@@ -20,7 +20,7 @@ int main(int argc, char** argv) {
   }
   if (argc == 7 && !std::strcmp(argv[1], "fused")) {
     std::printf("%d\n", (int)aim::anterp_in_rows(std::atoi(argv[2]), std::atoi(argv[3]) != 0, std::atoi(argv[4]),
-                                                 std::atoi(argv[5]), std::atoi(argv[6])));
+                                                 std::atoi(argv[5]), std::atoi(argv[6]) != 0));
     return 0;
   }
   if (argc == 6 && !std::strcmp(argv[1], "few")) {
