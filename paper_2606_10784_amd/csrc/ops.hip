@@ -582,8 +582,10 @@ __device__ double2 grid_pair(const NearGroup& g, const double* Wi, const double*
 // evaluations) as the kernel's length, with most of the chip idle: 5.4 ms for
 // the entries of 3 328 pulses (1.0 ms here), 3.2 ms for 512 (0.42), 18.8 ms for
 // 16 384 (5.6), 80 ms for 20 001 hats (28.8).  Bound by FP64 issue in the
-// Bessel functions; two waves per SIMD (the function's own registers would
-// leave one wave per SIMD: 1.6 ms; three or four spill: 1.0 to 1.2 ms).
+// Bessel functions.  Held to two waves per SIMD, which spills 122 of its
+// VGPRs (scratch 2.2 KB a lane, 1.7 of it the box stack of disjoint pairs);
+// without spills one wave per SIMD fits: 1.6 ms; three or four waves spill
+// more: 1.0 to 1.2 ms.
 __global__ __launch_bounds__(kNearBlock, 2) void k_near_build(
     NearGeo G, int basis, int64_t nnz, const int32_t* __restrict__ rows, const int32_t* __restrict__ cols,
     const int32_t* __restrict__ anx, const int32_t* __restrict__ any, const double* W0, const double* W1,
