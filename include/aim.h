@@ -51,7 +51,7 @@ typedef enum {
   AIM_OK = 0,
   AIM_E_ARG = 1,      /* invalid argument (null pointer, size, enum)          */
   AIM_E_GEOM = 2,     /* a stencil leaves the m x m grid                       */
-  AIM_E_OOM = 3,      /* device allocation failed                              */
+  AIM_E_OOM = 3,      /* device allocation failed, or set-up's host tables     */
   AIM_E_HIP = 4,      /* HIP runtime error                                     */
   AIM_E_STATE = 5,    /* call not valid in this context state                  */
   AIM_E_NOCONV = 6,   /* GMRES reached maxit; x holds the best iterate         */

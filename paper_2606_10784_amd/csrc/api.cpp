@@ -1,6 +1,7 @@
 // C ABI of libaim (declared in include/aim.h).
 #include <cmath>
 #include <cstdio>
+#include <exception>
 #include <new>
 #include <vector>
 
@@ -124,6 +125,15 @@ size_t footprint(const aim_params* p, int restart, const HostTables* t) {
   return b;
 }
 
+// The tables of set-up are std::vectors: no exception leaves a C entry.
+template <typename F> static aim_status host_memory(F&& f) {
+  try {
+    return f();
+  } catch (const std::exception&) {   // bad_alloc, length_error
+    return AIM_E_OOM;
+  }
+}
+
 }  // namespace aim
 
 extern "C" {
@@ -166,17 +176,16 @@ aim_status aim_setup(const aim_params* p, aim_ctx* out) {
   aim_ctx_s* h = new (std::nothrow) aim_ctx_s();
   if (!h) return AIM_E_OOM;
   Ctx* c = &h->c;
-  std::string err;
-  aim_status st = build_host_tables(p, c->t, err);
-  std::vector<double> rxy;
-  aim_params q;
-  if (st == AIM_OK && p->dual) {
+  aim_status st = host_memory([&] {
+    std::string err;
+    const aim_status host = build_host_tables(p, c->t, err);
+    if (host != AIM_OK || !p->dual) return host;
     // host tables of the dual hat space before any device work
-    rxy = refined_xy(p);
-    q = dual_params(p, rxy);
+    const std::vector<double> rxy = refined_xy(p);
+    const aim_params q = dual_params(p, rxy);
     c->dual = new (std::nothrow) Ctx();
-    st = c->dual ? build_host_tables(&q, c->dual->t, err) : AIM_E_OOM;
-  }
+    return c->dual ? build_host_tables(&q, c->dual->t, err) : AIM_E_OOM;
+  });
   if (st != AIM_OK) {
     delete c->dual;
     c->dual = nullptr;
@@ -195,12 +204,15 @@ aim_status aim_setup(const aim_params* p, aim_ctx* out) {
     delete h;
     return AIM_E_HIP;
   }
-  st = setup_device(c);
-  if (st == AIM_OK && c->dual) {
-    c->dual->device = c->device;
-    st = setup_device(c->dual);
-    if (st == AIM_OK) st = setup_dual(c);
-  }
+  st = host_memory([&] {
+    aim_status dev = setup_device(c);
+    if (dev == AIM_OK && c->dual) {
+      c->dual->device = c->device;
+      dev = setup_device(c->dual);
+      if (dev == AIM_OK) dev = setup_dual(c);
+    }
+    return dev;
+  });
   if (st == AIM_OK && p->max_restart > 0 && c->t.node_order == 0) {
     // the Krylov workspace of aim_solve: the caller's, or allocated here once
     void* ws = p->workspace;
