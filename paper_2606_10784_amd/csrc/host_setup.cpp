@@ -14,7 +14,6 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>
-#include <memory>
 
 #include "aim_internal.h"
 
@@ -116,10 +115,7 @@ static aim_status near_zone(HostTables& t) {
     std::vector<int32_t> fill(start.begin(), start.end() - 1);
     for (int q = 0; q < N; ++q) ord[fill[t.anc_y[byx[q]]]++] = byx[q];
   }
-  // [basis][dy]: from, to in ord; calloc, so that cell rows without bases take no memory
-  std::unique_ptr<int32_t, decltype(&std::free)> mem((int32_t*)std::calloc((size_t)N * D * 2, 4), &std::free);
-  int32_t* range = mem.get();
-  if (!range) return AIM_E_OOM;
+  std::vector<int32_t> range((size_t)N * D * 2, 0);   // [basis][dy]: from, to in ord
   t.nr_ptr.assign(N + 1, 0);
   int64_t total = 0;
   for (int y = 0; y < m; ++y) {
