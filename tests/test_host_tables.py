@@ -129,8 +129,3 @@ def test_host_errors(dumper, tmp_path):
     assert _run(dumper, t, bad, wl.K0, 0, 64, 0.1)["status"] == AIM_E_ARG
     bad[5, 0] = np.nan
     assert _run(dumper, t, bad, wl.K0, 0, 64, 0.1)["status"] == AIM_E_ARG
-
-
-def test_near_pairs_past_the_row_pointers(dumper, tmp_path):
-    """46 341 bases inside one near zone have more than 2^31 - 1 near pairs, past what the row pointers count: refused."""
-    assert _run(dumper, str(tmp_path), wl.circle(0.45, 46341), wl.K0, 0, 16, 0.1, near_radius=12)["status"] == AIM_E_ARG
